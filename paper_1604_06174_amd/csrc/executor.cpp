@@ -114,6 +114,9 @@ struct Exec {
 
   void backward_segment(int32_t lo, int32_t hi, const void *x, const std::vector<void *> &saved,
                         const std::vector<void *> &out) {
+    c.seg_saved = &saved;
+    c.seg_lo = lo;
+    c.ready_lo = c.ready_hi = 0;
     for (int32_t i = hi - 1; i >= lo; --i) {
       const void *xi = (i == lo) ? x : out[size_t(i - lo - 1)];
       void *dx = (i > 0) ? gslot[cur ^ 1] : nullptr;
@@ -121,6 +124,7 @@ struct Exec {
       ++bwd_count;
       cur ^= 1;
     }
+    c.seg_saved = nullptr;
   }
 
   void one_level(const Plan &p, const void *x0) {

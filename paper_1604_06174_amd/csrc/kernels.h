@@ -217,14 +217,11 @@ int gemm_bf16_col_blocks(int M, int N);
 int gemm_bf16_tiles(int M, int N);
 // Split-K for short, wide products: gemm_bf16_part writes `splits` partial
 // [M, N] products (contiguous slices) of op(A) op(B) over consecutive k
-// ranges; sum_slices adds nslices such slices in order, then D and bias:
-// C = sum_z part[z] (+ D) (+ bias[n]).  N must be a multiple of 4.
+// ranges, to be added in order.
 // (splits chosen so that about `target` workgroups run, at least 128 k each)
 int gemm_bf16_splits(int M, int N, int K, int target = 512);
 void gemm_bf16_part(hipStream_t s, int M, int N, int K, const void *A, bool a_fp32, int lda, bool ak,
                     const void *B, int ldb, bool bk, float *part, int splits);
-void sum_slices(hipStream_t s, const float *part, int nslices, int M, int N, float *C, int ldc,
-                const float *D = nullptr, int ldd = 0, const float *bias = nullptr);
 // k per split of gemm_bf16_part over K with `splits` splits
 int gemm_bf16_kper(int K, int splits);
 // gemm_bf16_part of [A1 | A2] (bf16, k contiguous, K1 + K2 columns) times B
@@ -269,31 +266,41 @@ void transpose_bf16(hipStream_t s, int R, int C, const float *src, void *dst, in
 void cvt_bf16(hipStream_t s, int64_t n, const float *src, void *dst);
 // dst (bf16, row stride ld) = src [R][C] fp32
 void cvt_bf16_rows(hipStream_t s, int R, int C, const float *src, void *dst, int ld);
-// Split-K inputs: zpart / lpart / dhpart hold ns partial slices of the
-// product, added in slice order before the bias (or the incoming dh), exactly
-// as sum_slices would.
-void lstm_fwd_point(hipStream_t s, int B, int H, const float *zpart, int ns, const float *bias,
-                    const float *c_prev, float *gates, void *h_out, float *c_out);
 // Softmax cross-entropy rows: loss_rows[r] = logsumexp(l[r]) - l[r][label],
 // dlog = (softmax - onehot) * scale, from the logits [rows, V] (bias
 // included) and the per row and column tile (max, sum of exp) pairs that
 // GEMM_EPI_ROWSOFTMAX wrote (nt tiles per row); V % 4 == 0.
-void softmax_ce_tiles(hipStream_t s, int rows, int V, const float *logits, int nt, const float *rstat,
-                      const int *labels, float scale, float *dlog, float *loss_rows);
-// the same over nunits units at once, in place (dlog over the logits): unit u's
+// nunits units at once, in place (dlog over the logits): unit u's
 // logits at logits + u ul, statistics at rstat + u ur, labels and loss rows at
 // + u rows
 void softmax_ce_tiles_batched(hipStream_t s, int nunits, int rows, int V, float *logits, int64_t ul, int nt,
                               const float *rstat, int64_t ur, const int *labels, float scale,
                               float *loss_rows);
-void head_bwd_prep(hipStream_t s, int B, int V, const float *dlog, void *dl_bf, float *db_o, bool first);
-// dbp receives ceil(B/4) records [4H] of bias-gradient column sums (one per
-// block of 4 batch rows); db_chunk adds a run of such records into db.
-// dh = the ns split-K slices [B, H] of the product that forms it, in order.
-void lstm_bwd_point(hipStream_t s, int B, int H, const float *dhpart, int ns, const float *dc_in,
-                    const float *gates, const float *c_t, const float *c_prev, const void *h_prev,
-                    const void *h_t, void *dz, float *dc_prev, void *hp_copy, void *hc_copy,
-                    float *dbp);
+// Steps' softmax gradients for the backward, step u = 0 .. nu-1 at dlog - u sd
+// (fp32 [B, V]): their bf16 copies at dl - u B V, their column sums to cs
+// [nu][V], and db (+)= those, in order of u.
+void head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t sd, void *dl, float *cs,
+               float *db, bool first);
+// ---- one LSTM step per launch (lstm_step.hip) ----
+// The weights in the steps' operand order (bf16): (E + H) 4H values of [W_x;
+// W_h], and the 4H H values of W_h.
+void lstm_pack_gates(hipStream_t s, int E, int H, const float *wx, const float *wh, void *dst);
+void lstm_pack_rows(hipStream_t s, int H, const float *wh, void *dst);
+// Forward: z = [x | h] [W_x; W_h] + b (x [B, E], h [B, H] bf16 or null, w
+// from lstm_pack_gates), gates [B, 4H], c_out, h_out.
+void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void *h, const void *w,
+                   const float *bias, const float *c_prev, float *gates, void *h_out,
+                   float *c_out);
+// Backward: dh = the ns slices of hpart ([B, H], `slice` floats apart) in
+// order + dzn [B, 4H] (bf16, may be null) times W_h^T (w from
+// lstm_pack_rows); then the gate backward.  dz must not overlap dzn.  dbp receives
+// lstm_step_row_blocks(B) records [4H] of bias-gradient column sums (one per
+// block of 16 batch rows); db_chunk adds a run of such records into db.
+int lstm_step_row_blocks(int B);
+void lstm_step_bwd(hipStream_t s, int B, int H, const void *dzn, const void *w,
+                   const float *hpart, int ns, int64_t slice, const float *dc_in, const float *gates,
+                   const float *c_t, const float *c_prev, const void *h_prev, const void *h_t, void *dz,
+                   float *dc_prev, void *hp_copy, void *hc_copy, float *dbp);
 void db_chunk(hipStream_t s, int N, int nrec, const float *rec, float *db, bool first);
 void loss_reduce(hipStream_t s, int64_t rows, const float *v, float scale, float *loss);
 void fill_f32(hipStream_t s, int64_t n, float *p, float v);

@@ -1,10 +1,8 @@
-// Pointwise and row kernels of the LSTM step with its softmax head.
-//   gates  i, f, g, o = sigma(z_i), sigma(z_f), tanh(z_g), sigma(z_o)
-//          (z columns [0,H), [H,2H), [2H,3H), [3H,4H))
-//   cell   c_t = f c_{t-1} + i g,   h_t = o tanh(c_t)   (c fp32, h rounded to bf16)
+// Row kernels of the LSTM's softmax head, weight copies and reductions (the
+// recurrence itself is in lstm_step.hip).
 //   head   softmax cross-entropy of a [B, V] row block; the gradient
 //          (p - onehot) * scale is kept in fp32
-// Every sum (split-K slices, bias-gradient columns) runs in an order fixed by
+// Every sum runs in an order fixed by
 // the shapes alone, so a step is bit-reproducible whatever the schedule.
 #include <hip/hip_runtime.h>
 
@@ -13,34 +11,6 @@
 
 namespace ckpt {
 namespace {
-
-__device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
-
-// NV elements o[0..NV) of a split-K product: each element's ns partial
-// slices (slice stride `slice`) added in slice order -- the order sum_slices
-// uses.  Slices are fetched U at a time for all NV elements before any of
-// them is added, so the loads of a round are in flight together.
-template <int NV, int U>
-__device__ __forceinline__ void slices_sum(const float *__restrict__ part, int ns, size_t slice,
-                                           const size_t (&o)[NV], float (&v)[NV]) {
-#pragma unroll
-  for (int k = 0; k < NV; ++k) v[k] = part[o[k]];
-  int z = 1;
-  for (; z + U <= ns; z += U) {
-    float t[U][NV];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int k = 0; k < NV; ++k) t[u][k] = part[(z + u) * slice + o[k]];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int k = 0; k < NV; ++k) v[k] += t[u][k];
-  }
-  for (; z < ns; ++z)
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] += part[z * slice + o[k]];
-}
 
 // dst[c][r] = bf16(src[r][c]) for src [R][C] fp32, through 32x32 LDS tiles.
 __global__ __launch_bounds__(256) void k_transpose_bf16(int R, int C, const float *__restrict__ src,
@@ -90,35 +60,6 @@ __global__ __launch_bounds__(256) void k_cvt_bf16_rows(int R, int C, const float
   const int64_t n = int64_t(R) * C;
   for (int64_t e = blockIdx.x * int64_t(256) + threadIdx.x; e < n; e += int64_t(gridDim.x) * 256)
     dst[(e / C) * ld + e % C] = (__bf16)src[e];
-}
-
-// one thread per (b, j); z = sum of the ns partial slices [B, 4H] + bias
-__global__ __launch_bounds__(256) void k_lstm_fwd_point(int B, int H, const float *__restrict__ zpart,
-                                                        int ns, const float *__restrict__ bias,
-                                                        const float *__restrict__ c_prev,
-                                                        float *__restrict__ gates,
-                                                        __bf16 *__restrict__ h_out,
-                                                        float *__restrict__ c_out) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= B * H) return;
-  const int b = e / H, j = e % H;
-  const size_t r = size_t(b) * 4 * H + j;
-  const size_t o[4] = {r, r + H, r + 2 * H, r + 3 * H};
-  float z[4];
-  slices_sum<4, 4>(zpart, ns, size_t(B) * 4 * H, o, z);
-  const float ig = sigm(z[0] + bias[j]);
-  const float fg = sigm(z[1] + bias[H + j]);
-  const float gg = tanhf(z[2] + bias[2 * H + j]);
-  const float og = sigm(z[3] + bias[3 * H + j]);
-  const float cp = c_prev ? c_prev[e] : 0.f;
-  const float c = fg * cp + ig * gg;
-  float *gr = gates + size_t(b) * 4 * H;
-  gr[j] = ig;
-  gr[H + j] = fg;
-  gr[2 * H + j] = gg;
-  gr[3 * H + j] = og;
-  c_out[e] = c;
-  h_out[e] = (__bf16)(og * tanhf(c));
 }
 
 // (m, s) <- the pair for the union of two column sets: m the larger maximum,
@@ -176,101 +117,6 @@ __global__ __launch_bounds__(256) void k_softmax_ce_tiles(int V, const float *lo
     *reinterpret_cast<float4 *>(dlog + size_t(row) * V + v0) = make_float4(d[0], d[1], d[2], d[3]);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0 && !(lab >= 0 && lab < V)) loss_rows[row] = NAN;
-}
-
-// Workgroup = 32 columns x 16 row groups, so V = 10000 gives 313 workgroups,
-// more than there are compute units; group rg takes rows b = rg, rg + 16, ...,
-// issuing four row loads before it uses any, and adds them in row order.  The
-// column sums of the groups are combined as a fixed pairwise tree.
-
-// dl_bf[b][v] = bf16(dlog[b][v]);  db_o[v] (+)= sum_b dlog[b][v]
-__global__ __launch_bounds__(512) void k_head_bwd_prep(int B, int V, const float *__restrict__ dlog,
-                                                       __bf16 *__restrict__ dl_bf,
-                                                       float *__restrict__ db_o, int first) {
-  __shared__ float part[16][32];
-  const int cx = threadIdx.x & 31, rg = threadIdx.x >> 5;
-  const int v = blockIdx.x * 32 + cx;
-  float s = 0.f;
-  if (v < V)
-    for (int b0 = rg; b0 < B; b0 += 64) {
-      float d[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int b = b0 + 16 * u;
-        d[u] = b < B ? dlog[size_t(b) * V + v] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int b = b0 + 16 * u;
-        if (b < B) {
-          dl_bf[size_t(b) * V + v] = (__bf16)d[u];
-          s += d[u];
-        }
-      }
-    }
-  part[rg][cx] = s;
-  __syncthreads();
-  if (rg == 0 && v < V) {
-    float q[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) q[i] = part[2 * i][cx] + part[2 * i + 1][cx];
-    const float t = (((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
-    db_o[v] = first ? t : db_o[v] + t;
-  }
-}
-
-// Gate backward, one thread per (b, j): workgroup = 64 hidden units x 4
-// batch rows (blockIdx.y = row block).  dh = the ns partial slices [B, H] of
-// the product that forms it (head gradient and, but for the last step, the
-// next step's dz W_h^T), added in order.
-// The workgroup's bias-gradient column sums over its 4 rows, ((r0 + r1) + r2)
-// + r3, go to dbp[blockIdx.y][4H]; k_db_chunk adds them up.
-__global__ __launch_bounds__(256) void k_lstm_bwd_point(int B, int H, const float *__restrict__ dhpart,
-                                                        int ns, const float *__restrict__ dc_in,
-                                                        const float *__restrict__ gates,
-                                                        const float *__restrict__ c_t,
-                                                        const float *__restrict__ c_prev,
-                                                        const __bf16 *__restrict__ h_prev,
-                                                        const __bf16 *__restrict__ h_t,
-                                                        __bf16 *__restrict__ dz,
-                                                        float *__restrict__ dc_prev,
-                                                        __bf16 *__restrict__ hp_copy,
-                                                        __bf16 *__restrict__ hc_copy,
-                                                        float *__restrict__ dbp) {
-  __shared__ float part[4][4][64];
-  const int cx = threadIdx.x & 63, rg = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + cx, b = blockIdx.y * 4 + rg;
-  float zv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (j < H && b < B) {
-    const size_t e = size_t(b) * H + j;
-    const size_t oe[1] = {e};
-    float dh[1];
-    slices_sum<1, 8>(dhpart, ns, size_t(B) * H, oe, dh);
-    const float dhv = dh[0];
-    const float *gr = gates + size_t(b) * 4 * H;
-    const float ig = gr[j], fg = gr[H + j], gg = gr[2 * H + j], og = gr[3 * H + j];
-    const float tc = tanhf(c_t[e]);
-    const float dct = dc_in[e] + dhv * og * (1.f - tc * tc);
-    const float cp = c_prev ? c_prev[e] : 0.f;
-    zv[0] = dct * gg * ig * (1.f - ig);
-    zv[1] = dct * cp * fg * (1.f - fg);
-    zv[2] = dct * ig * (1.f - gg * gg);
-    zv[3] = dhv * tc * og * (1.f - og);
-    __bf16 *dr = dz + size_t(b) * 4 * H;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) dr[k * H + j] = (__bf16)zv[k];
-    if (dc_prev) dc_prev[e] = dct * fg;
-    hp_copy[e] = h_prev ? h_prev[e] : (__bf16)0.f;
-    hc_copy[e] = h_t[e];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) part[k][rg][cx] = zv[k];
-  __syncthreads();
-  if (j < H) {
-    const int k = rg;  // row group rg writes gate k's column sum
-    const float t = ((part[k][0][cx] + part[k][1][cx]) + part[k][2][cx]) + part[k][3][cx];
-    dbp[size_t(blockIdx.y) * 4 * H + size_t(k) * H + j] = t;
-  }
 }
 
 // db[n] (+)= the nrec records rec[r][n] (record stride N), r = 0 .. nrec-1:
@@ -347,21 +193,6 @@ void cvt_bf16(hipStream_t s, int64_t n, const float *src, void *dst) {
   hipLaunchKernelGGL(k_cvt_bf16, dim3(grid_for(n)), dim3(256), 0, s, n, src, static_cast<__bf16 *>(dst));
 }
 
-void lstm_fwd_point(hipStream_t s, int B, int H, const float *zpart, int ns, const float *bias,
-                    const float *c_prev, float *gates, void *h_out, float *c_out) {
-  hipLaunchKernelGGL(k_lstm_fwd_point, dim3((B * H + 255) / 256), dim3(256), 0, s, B, H, zpart, ns,
-                     bias, c_prev, gates, static_cast<__bf16 *>(h_out), c_out);
-}
-
-void softmax_ce_tiles(hipStream_t s, int rows, int V, const float *logits, int nt, const float *rstat,
-                      const int *labels, float scale, float *dlog, float *loss_rows) {
-  if (V % 4 != 0 || reinterpret_cast<uintptr_t>(logits) % 16 != 0 ||
-      reinterpret_cast<uintptr_t>(dlog) % 16 != 0)
-    fail(CKPT_E_INVALID, "softmax_ce_tiles: V must be a multiple of 4 and the rows 16-byte aligned");
-  hipLaunchKernelGGL(k_softmax_ce_tiles, dim3((V + 1023) / 1024, rows), dim3(256), 0, s, V, logits, nt,
-                     rstat, labels, scale, dlog, loss_rows, rows, int64_t(0), int64_t(0));
-}
-
 void softmax_ce_tiles_batched(hipStream_t s, int nunits, int rows, int V, float *logits, int64_t ul, int nt,
                               const float *rstat, int64_t ur, const int *labels, float scale,
                               float *loss_rows) {
@@ -370,21 +201,6 @@ void softmax_ce_tiles_batched(hipStream_t s, int nunits, int rows, int V, float 
     fail(CKPT_E_INVALID, "softmax_ce_tiles_batched: V and the unit stride multiples of 4, rows 16-byte aligned");
   hipLaunchKernelGGL(k_softmax_ce_tiles, dim3((V + 1023) / 1024, rows, nunits), dim3(256), 0, s, V, logits,
                      nt, rstat, labels, scale, logits, loss_rows, rows, ul, ur);
-}
-
-void head_bwd_prep(hipStream_t s, int B, int V, const float *dlog, void *dl_bf, float *db_o, bool first) {
-  hipLaunchKernelGGL(k_head_bwd_prep, dim3((V + 31) / 32), dim3(512), 0, s, B, V, dlog,
-                     static_cast<__bf16 *>(dl_bf), db_o, first ? 1 : 0);
-}
-
-void lstm_bwd_point(hipStream_t s, int B, int H, const float *dhpart, int ns, const float *dc_in,
-                    const float *gates, const float *c_t, const float *c_prev, const void *h_prev,
-                    const void *h_t, void *dz, float *dc_prev, void *hp_copy, void *hc_copy,
-                    float *dbp) {
-  hipLaunchKernelGGL(k_lstm_bwd_point, dim3((H + 63) / 64, (B + 3) / 4), dim3(256), 0, s, B, H, dhpart,
-                     ns, dc_in, gates, c_t, c_prev, static_cast<const __bf16 *>(h_prev),
-                     static_cast<const __bf16 *>(h_t), static_cast<__bf16 *>(dz), dc_prev,
-                     static_cast<__bf16 *>(hp_copy), static_cast<__bf16 *>(hc_copy), dbp);
 }
 
 void db_chunk(hipStream_t s, int N, int nrec, const float *rec, float *db, bool first) {

@@ -217,6 +217,12 @@ struct StepCtx {
   // unit's backward, so a unit's forward may keep transient tensors there
   char *q = nullptr;
   uint64_t launches = 0;
+  // the kept segment being back-propagated: unit seg_lo + k's saved internals
+  // at (*seg_saved)[k] (null outside a segment's backward), and the units
+  // [ready_lo, ready_hi) of it for which the net has already done the part of
+  // their backwards that it does for several units at once
+  const std::vector<void *> *seg_saved = nullptr;
+  int32_t seg_lo = 0, ready_lo = 0, ready_hi = 0;
   // false while a forward sweep runs whose saved internals are discarded
   // (they are formed again by the unit's re-run before its backward)
   bool keep_saved = true;

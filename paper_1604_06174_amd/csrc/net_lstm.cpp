@@ -45,12 +45,14 @@ class LstmNet : public Net {
   uint64_t hb, cb;  // boundary parts
   uint64_t ga, da;  // saved parts: gates, dlog
   // operator workspace offsets
-  uint64_t k_wcat, k_wot, k_wob, k_dbp, k_lossrows, k_loss, k_part, k_rstat;
-  bool zcat;  // z = [x_t | h_{t-1}] [W_x; W_h] as one product (same slices as the two)
-  // split-K counts: input and recurrent parts of z, the last step's dh (head
-  // only), every other step's dh (head and recurrence in one product); the
-  // logits are one product (their softmax statistics come from its epilogue)
-  int s_x, s_h, s_dh, s_dm;
+  uint64_t k_wcat, k_wot, k_wob, k_dbp, k_lossrows, k_loss, k_buf;
+  // floats of k_buf: during a segment's heads the logits' row statistics,
+  // during its backwards the head slices and, at its end, the column sums of
+  // the softmax gradients of the steps they were formed for
+  uint64_t buf_floats;
+  int s_head;  // k slices of dl_t W_o^T
+  int nb;      // steps per batched head gradient
+  int s_one;   // k slices of [dl_t | dz_{t+1}] [W_o; W_h], chunks of one step
   // extra gradient buffer offsets
   uint64_t x_dz, x_dl, x_hp, x_hc;
 
@@ -88,35 +90,31 @@ class LstmNet : public Net {
     x_hc = take(uint64_t(C) * B * H * 2);
     grad_extra = off;
     off = 0;
-    k_wcat = take(uint64_t(E + H) * 4 * H * 2);  // [4H][E + H]: W_x^T | W_h^T
-
+    k_wcat = take(uint64_t(E + H) * 4 * H * 2);  // [W_x; W_h] packed
     k_wot = take(uint64_t(H) * V * 2);
-    k_wob = take(uint64_t(H) * (V + 4 * H) * 2);  // [H][V + 4H]: W_o | W_h
+    // [H][V] W_o and the packed W_h; chunks of one step: [H][V + 4H], W_o | W_h
+    k_wob = take(uint64_t(H) * (V + 4 * H) * 2);
     // bias-gradient column sums of one chunk: per step, one [4H] record per
-    // block of 4 batch rows
-    k_dbp = take(uint64_t(C) * ((B + 3) / 4) * 4 * H * 4);
+    // row block of the step kernel
+    k_dbp = take(uint64_t(C) * lstm_step_row_blocks(B) * 4 * H * 4);
     k_lossrows = take(uint64_t(T) * B * 4);
     k_loss = take(4);
-    // z's slices are read back by the pointwise launch right away, so it takes
-    // fewer, longer splits (about 128 workgroups per part: 256 for z over
-    // [x_t | h_{t-1}] at the 1024/1024/64 shape, 4 slices instead of 16); the
-    // backward's products keep about 512 workgroups.
-    s_x = gemm_bf16_splits(B, 4 * H, E, 128);
-    s_h = gemm_bf16_splits(B, 4 * H, H, 128);
-    // one launch for both parts of z when its k splits fall exactly on the two
-    // parts' own splits (then every slice holds the same sums in the same order)
-    zcat = E == H && s_x == s_h && gemm_bf16_kper(E, s_x) * s_x == E &&
-           gemm_bf16_kper(E + H, s_x + s_h) == gemm_bf16_kper(E, s_x) && E % 8 == 0;
-    s_dh = gemm_bf16_splits(B, H, V);
-    s_dm = gemm_bf16_splits(B, H, V + 4 * H);
-    const uint64_t part = std::max({uint64_t(s_x + s_h) * B * 4 * H, uint64_t(B) * V,
-                                    uint64_t(std::max(s_dh, s_dm)) * B * H});
-    k_part = take(part * 4);
-    k_rstat = take(uint64_t(HG) * B * gemm_bf16_col_blocks(B, V) * 2 * 4);
+    // head slices: four (or fewer where V is short), which give a batch of
+    // seven steps 448 workgroups at the 1024/10000/64 shape and a single
+    // step's product (recursive plans) 128; as many steps at once as the row
+    // statistics' buffer and eight [B, H] tensors (or one of logits) hold
+    s_head = std::min(4, gemm_bf16_splits(B, H, V));
+    s_one = C == 1 ? gemm_bf16_splits(B, H, V + 4 * H) : 0;
+    const uint64_t BH = uint64_t(B) * H, BV = uint64_t(B) * V;
+    buf_floats = std::max(std::max(BV, 8 * BH) + uint64_t(HG) * B * gemm_bf16_col_blocks(B, V) * 2,
+                          s_one * BH + V);
+    nb = int(std::min<uint64_t>(std::min(C, HG), buf_floats / (s_head * BH + V)));
+    k_buf = take(buf_floats * 4);
     ks_bytes = off;
     timed_family = "k_gemm_bf16";
   }
 
+  int ld_wo() const { return C > 1 ? V : V + 4 * H; }
   char *K(StepCtx &c, uint64_t o) const { return c.ks + o; }
   float *Kf(StepCtx &c, uint64_t o) const { return reinterpret_cast<float *>(c.ks + o); }
   char *X(StepCtx &c, uint64_t o) const { return c.gextra + o; }
@@ -131,25 +129,28 @@ class LstmNet : public Net {
               2.0 * (double(M) * Kd + double(Kd) * N) + (epi == GEMM_EPI_ADD ? 8.0 : 4.0) * M * N);
     c.launches += 1;
   }
-  // split-K partial products into slices [z0, z0 + splits) of the partial buffer.
+  // split-K partial products into the slices of k_buf.
   // Algorithmic bytes: each operand read once and the product written once
   // (the slices are this implementation's, not the product's, traffic).
   void gemm_part(StepCtx &c, int M, int N, int Kd, const void *A, int lda, const void *Bm, int ldb,
-                 int z0, int splits) {
+                 int splits) {
     timer.begin(c.s);
     gemm_bf16_part(c.s, M, N, Kd, A, false, lda, true, Bm, ldb, true,
-                   Kf(c, k_part) + size_t(z0) * M * N, splits);
+                   Kf(c, k_buf), splits);
     timer.end(c.s, 2.0 * M * N * Kd, 2.0 * (double(M) * Kd + double(Kd) * N) + 4.0 * M * N);
     c.launches += 1;
   }
 
   void begin_step(StepCtx &c) override {
-    // bf16 copies of the weights in the layouts the GEMMs read (k contiguous)
-    transpose_bf16(c.s, E, 4 * H, P(c, pWx), K(c, k_wcat), E + H);              // [4H][0, E)
-    transpose_bf16(c.s, H, 4 * H, P(c, pWh), K(c, k_wcat) + size_t(E) * 2, E + H);  // [4H][E, E + H)
-    cvt_bf16_rows(c.s, H, 4 * H, P(c, pWh), K(c, k_wob) + size_t(V) * 2, V + 4 * H);  // [H][V, V + 4H)
+    // bf16 copies of the weights: in the step kernels' operand order, and
+    // k contiguous for the GEMMs
+    lstm_pack_gates(c.s, E, H, P(c, pWx), P(c, pWh), K(c, k_wcat));
     transpose_bf16(c.s, H, V, P(c, pWo), K(c, k_wot));        // [V][H]
-    cvt_bf16_rows(c.s, H, V, P(c, pWo), K(c, k_wob), V + 4 * H);                    // [H][0, V)
+    cvt_bf16_rows(c.s, H, V, P(c, pWo), K(c, k_wob), ld_wo());                    // [H][0, V)
+    if (C > 1)
+      lstm_pack_rows(c.s, H, P(c, pWh), K(c, k_wob) + size_t(H) * V * 2);
+    else
+      cvt_bf16_rows(c.s, H, 4 * H, P(c, pWh), K(c, k_wob) + size_t(V) * 2, ld_wo());  // [H][V, V + 4H)
     c.launches += 5;
   }
 
@@ -158,23 +159,9 @@ class LstmNet : public Net {
     char *y = static_cast<char *>(yv);
     char *sv = static_cast<char *>(saved);
     const void *xt = static_cast<const char *>(c.input) + size_t(i) * B * E * 2;
-    // z = x_t W_x + h_{t-1} W_h + b: both products split over k into one
-    // slice buffer that the pointwise kernel adds up in order with the bias
-    if (i > 0 && zcat) {
-      timer.begin(c.s);
-      gemm_bf16_part_cat(c.s, B, 4 * H, E, xt, E, H, x, H, K(c, k_wcat), E + H, Kf(c, k_part),
-                         s_x + s_h);
-      timer.end(c.s, 2.0 * B * 4 * H * (E + H),
-                2.0 * (double(B) * (E + H) + double(E + H) * 4 * H) + 4.0 * B * 4 * H);
-      c.launches += 1;
-    } else {
-      gemm_part(c, B, 4 * H, E, xt, E, K(c, k_wcat), E + H, 0, s_x);
-      if (i > 0) gemm_part(c, B, 4 * H, H, x, H, K(c, k_wcat) + size_t(E) * 2, E + H, s_x, s_h);
-    }
-    const float *c_prev = i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr;
-    float *gates = reinterpret_cast<float *>(sv);
-    lstm_fwd_point(c.s, B, H, Kf(c, k_part), s_x + (i > 0 ? s_h : 0), P(c, pb), c_prev, gates, y,
-                   reinterpret_cast<float *>(y + hb));
+    lstm_step_fwd(c.s, B, H, E, xt, i > 0 ? x : nullptr, K(c, k_wcat), P(c, pb),
+                  i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr, reinterpret_cast<float *>(sv), y,
+                  reinterpret_cast<float *>(y + hb));
     c.launches += 1;
     // the step's head runs after the kept forward of its segment (fwd_segment)
   }
@@ -186,10 +173,10 @@ class LstmNet : public Net {
     const int64_t ur = int64_t(B) * nt * 2;
     timer.begin(c.s);
     gemm_bf16_rowsoftmax_batched(c.s, nb, B, V, H, y0, H, sy, K(c, k_wot), H, dl0, sd, P(c, pbo),
-                                 Kf(c, k_rstat), ur);
+                                 Kf(c, k_buf), ur);
     // each step's h and logits once, the shared W_o once
     timer.end(c.s, 2.0 * nb * B * V * H, nb * (2.0 * B * H + 4.0 * B * V) + 2.0 * H * V);
-    softmax_ce_tiles_batched(c.s, nb, B, V, dl0, sd, nt, Kf(c, k_rstat), ur,
+    softmax_ce_tiles_batched(c.s, nb, B, V, dl0, sd, nt, Kf(c, k_buf), ur,
                              static_cast<const int *>(c.target) + size_t(i0) * B, 1.0f / (float(T) * float(B)),
                              Kf(c, k_lossrows) + size_t(i0) * B);
     c.launches += 2;
@@ -219,6 +206,30 @@ class LstmNet : public Net {
     }
   }
 
+  // bf16 softmax gradients (into the chunk buffer), output-bias gradient and
+  // dl_t W_o^T slices of step i and the steps before it that share its
+  // segment and its chunk, at most nb
+  void head_grads(int32_t i, const char *saved, StepCtx &c) {
+    const int t0 = (i / C) * C;
+    int lo = i;
+    int64_t sd = 0;  // from one step's saved internals to the next's
+    if (c.seg_saved && nb > 1) {
+      const auto at = [&](int t) { return static_cast<const char *>((*c.seg_saved)[size_t(t - c.seg_lo)]); };
+      const int first = std::max({t0, int(c.seg_lo), i - nb + 1});
+      if (first < i) sd = at(i) - at(i - 1);
+      while (lo > first && at(lo) - at(lo - 1) == sd) --lo;
+    }
+    const int nu = i - lo + 1;
+    char *dl = X(c, x_dl) + size_t(lo - t0) * B * V * 2;
+    head_prep(c.s, nu, B, V, reinterpret_cast<const float *>(saved + ga), sd / 4,
+              X(c, x_dl) + size_t(i - t0) * B * V * 2, Kf(c, k_buf) + buf_floats - uint64_t(nb) * V,
+              G(c, pbo), i == n - 1);
+    c.launches += 2;
+    if (C > 1) gemm_part(c, nu * B, H, V, dl, V, K(c, k_wob), ld_wo(), s_head);
+    c.ready_lo = lo;
+    c.ready_hi = i + 1;
+  }
+
   void bwd(int32_t i, const void *gv, void *dxv, const void *xv, const void *yv, const void *saved,
            void *qv, StepCtx &c) override {
     const char *g = static_cast<const char *>(gv);
@@ -229,39 +240,42 @@ class LstmNet : public Net {
     const uint64_t gh = align256(4ull * B * H);  // dh part of a gradient slot
     const int t0 = (i / C) * C;
     const size_t row = size_t(i - t0) * B;
-    const bool first_step = i == n - 1;
-    const int t_end = std::min(t0 + C, int(n)), rb = (B + 3) / 4;
-    char *dl = X(c, x_dl) + row * V * 2;
+    const bool last = i == n - 1;
+    const int t_end = std::min(t0 + C, int(n)), rb = lstm_step_row_blocks(B);
     char *dz = X(c, x_dz) + row * 4 * H * 2;
-    char *hp = X(c, x_hp) + row * H * 2;
-    char *hc = X(c, x_hc) + row * H * 2;
-    head_bwd_prep(c.s, B, V, reinterpret_cast<const float *>(sv + ga), dl, G(c, pbo), first_step);
     (void)qv;
-    // total dh = dl_t W_o^T + dz_{t+1} W_h^T (the incoming dh; none at the
-    // last step): one split-K product over [dl_t | dz_{t+1}] and [W_o | W_h],
-    // its slices added up by the gate backward.  dz_{t+1} is the next step's
-    // row of the chunk buffer (row 0 of it when t + 1 began a chunk; nothing
-    // has written that row since).
-    int ns = s_dh;
-    if (first_step) {
-      gemm_part(c, B, H, V, dl, V, K(c, k_wob), V + 4 * H, 0, s_dh);
-    } else {
-      const int t1 = i + 1;
-      const char *dzn = X(c, x_dz) + size_t(t1 - (t1 / C) * C) * B * 4 * H * 2;
-      timer.begin(c.s);
-      gemm_bf16_part_cat(c.s, B, H, V, dl, V, 4 * H, dzn, 4 * H, K(c, k_wob), V + 4 * H,
-                         Kf(c, k_part), s_dm);
-      timer.end(c.s, 2.0 * B * H * (V + 4.0 * H),
-                2.0 * (double(B) * (V + 4 * H) + double(V + 4 * H) * H) + 4.0 * B * H);
-      c.launches += 1;
-      ns = s_dm;
+    if (i < c.ready_lo || i >= c.ready_hi) head_grads(i, sv, c);
+    // dh = dl_t W_o^T + dz_{t+1} W_h^T.  dz_{t+1} is the next step's row of
+    // the chunk buffer (row 0 of it when t + 1 began a chunk: nothing has
+    // written that row since, and this step's row is another one unless a
+    // chunk is a single step, where both parts are formed by one product
+    // before the gate backward overwrites it)
+    const char *dzn = last ? nullptr : X(c, x_dz) + size_t((i + 1) % C) * B * 4 * H * 2;
+    const float *hp = Kf(c, k_buf) + size_t(i - c.ready_lo) * B * H;
+    int ns = s_head;
+    int64_t slice = int64_t(c.ready_hi - c.ready_lo) * B * H;
+    if (C == 1) {
+      const char *dl = X(c, x_dl);
+      slice = int64_t(B) * H;
+      if (last) {
+        gemm_part(c, B, H, V, dl, V, K(c, k_wob), ld_wo(), s_head);
+      } else {
+        timer.begin(c.s);
+        gemm_bf16_part_cat(c.s, B, H, V, dl, V, 4 * H, dzn, 4 * H, K(c, k_wob), ld_wo(), Kf(c, k_buf), s_one);
+        timer.end(c.s, 2.0 * B * H * (V + 4.0 * H),
+                  2.0 * (double(B) * (V + 4 * H) + double(V + 4 * H) * H) + 4.0 * B * H);
+        c.launches += 1;
+        ns = s_one;
+        dzn = nullptr;
+      }
     }
-    lstm_bwd_point(c.s, B, H, Kf(c, k_part), ns, reinterpret_cast<const float *>(g + gh),
-                   reinterpret_cast<const float *>(sv), reinterpret_cast<const float *>(y + hb),
-                   i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr, i > 0 ? x : nullptr, y, dz,
-                   dx ? reinterpret_cast<float *>(dx + gh) : nullptr, hp, hc,
-                   Kf(c, k_dbp) + size_t(t_end - 1 - i) * rb * 4 * H);
-    c.launches += 2;
+    lstm_step_bwd(c.s, B, H, dzn, K(c, k_wob) + size_t(H) * V * 2, hp, ns, slice,
+                  reinterpret_cast<const float *>(g + gh), reinterpret_cast<const float *>(sv),
+                  reinterpret_cast<const float *>(y + hb),
+                  i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr, i > 0 ? x : nullptr, y, dz,
+                  dx ? reinterpret_cast<float *>(dx + gh) : nullptr, X(c, x_hp) + row * H * 2,
+                  X(c, x_hc) + row * H * 2, Kf(c, k_dbp) + size_t(t_end - 1 - i) * rb * 4 * H);
+    c.launches += 1;
     if (i == t0) {  // the chunk [t0, t0 + C) is complete: its weight gradients
       const int rows = (t_end - t0) * B;
       const bool first_chunk = t0 + C >= n;

@@ -372,6 +372,8 @@ def dry_runs(quick):
                   drop_bn_relu=1, name="cifar small drop bn-relu"),
              dict(kind="lstm", T=13, batch=8, input=16, hidden=24, vocab=40, grad_chunk=4,
                   name="lstm small"),
+             dict(kind="lstm", T=7, batch=17, input=40, hidden=24, vocab=72, grad_chunk=1,
+                  name="lstm chunks of one step"),
              dict(kind="resnet_bottleneck", stage_blocks=(2, 1, 1, 1), widths=(8, 16, 32, 64),
                   stem_channels=16, image=32, batch=2, classes=10, name="bottleneck small"),
              dict(kind="resnet_bottleneck", stage_blocks=(2, 1, 1, 1), widths=(8, 16, 32, 64),
@@ -382,7 +384,7 @@ def dry_runs(quick):
     full = [("resnet1000", [(PL.GREEDY, "tenth", 0), (PL.NONE, 0, 0)]),
             ("resnet1000 drop bn-relu", [(PL.GREEDY, "tenth", 0)]),
             ("cifar110", [(PL.SQRT, 0, 0)]), ("mlp64", [(PL.SQRT, 8, 0)]),
-            ("lstm4096", [(PL.SQRT, 64, 0)]), ("mlp1024", [(PL.RECURSIVE, 0, 0)])]
+            ("lstm4096", [(PL.SQRT, 64, 0), (PL.RECURSIVE, 0, 0)]), ("mlp1024", [(PL.RECURSIVE, 0, 0)])]
     if quick:
         full = full[:1]
     for name, plans in full:

@@ -1,0 +1,26 @@
+"""The LSTM step kernels at the edges of their tiles and dispatch: the bars, plans
+and bit-identity checks of test_gpu_lstm on shapes with one row, one row past a
+16- and a 32-row tile, hidden sizes that leave a partial 16-column tile, k
+ranges on both sides of the four / sixteen wavefront rule with fewer k steps
+than wavefronts, an input of another size than the state, chunks of one step
+(where the recurrent product takes its own launch) and chunks that no batch of
+head gradients divides."""
+import pytest
+
+import test_gpu_lstm as base
+
+pytestmark = pytest.mark.gpu
+
+EDGES = {
+    "one_row": dict(T=5, batch=1, input=8, hidden=8, vocab=8, grad_chunk=2),
+    "rows17": dict(T=7, batch=17, input=40, hidden=24, vocab=72, grad_chunk=3),
+    "rows33_k520": dict(T=6, batch=33, input=456, hidden=64, vocab=136, grad_chunk=0),
+    "hidden136": dict(T=11, batch=16, input=16, hidden=136, vocab=304, grad_chunk=10),
+    "chunk1": dict(T=6, batch=5, input=24, hidden=40, vocab=56, grad_chunk=1),
+}
+
+
+@pytest.mark.parametrize("case", list(EDGES))
+def test_lstm_step_edges(case, monkeypatch):
+    monkeypatch.setitem(base.CASES, case, dict(EDGES[case], kind="lstm", seed=75))
+    base.test_lstm_step_parity_all_modes(case)
