@@ -34,22 +34,28 @@ void gemm_f32(hipStream_t s, int M, int N, int K, const float *A, int lda, bool 
               int ldb, bool tb, float *C, int ldc, int epi, const float *D = nullptr, int ldd = 0,
               const float *bias = nullptr, float *Z = nullptr, int ldz = 0);
 
-// Residual-MLP backward prologue: dr = g * [z > 0]; db[n] = sum_m dr[m, n]
-// (fixed summation order).  [rows, cols] row-major.
-// dr = g * [z > 0] and db = column sums of dr (rows in a fixed order); pdb is
-// workspace of mlp_relu_row_blocks(rows) * cols floats.
-int mlp_relu_row_blocks(int rows);
-void mlp_relu_bwd(hipStream_t s, int rows, int cols, const float *g, const float *z, float *dr,
-                  float *db, float *pdb);
+// Residual-MLP block backward, dr = g * [z > 0]: dW = x^T dr, dx = g + dr W^T
+// (none when dx is null), db = column sums of dr, in one launch (two more for
+// db from 1025 rows on); all [B, D] / [D, D] row-major.  pdb is workspace of
+// mlp_row_blocks(B) * D floats.  With z null g is dr itself and dx = dr W^T.
+// Returns the launches.
+int mlp_row_blocks(int rows);
+int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const float *x, const float *W,
+            float *dx, float *dW, float *db, float *pdb);
+// column sums of g [rows, cols] in the order of mlp_bwd's
+void mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb);
+// the same through partial sums of 16-row blocks (pdb), for many rows; g
+// counts where z > 0 when z is given
+void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb);
 
-// Mean-squared-error head: loss_out[0] = sum((y-t)^2)/count, g = 2 (y-t)/count.
-void mse_head(hipStream_t s, int64_t count, const float *y, const float *t, float *g,
-              float *loss_out);
+// Mean-squared-error head: loss_out[0] = sum((y-t)^2)/count, g = 2 (y-t)/count;
+// part is workspace of mse_blocks(count) floats.  Returns the launches.
+int mse_blocks(int64_t count);
+int mse_head(hipStream_t s, int64_t count, const float *y, const float *t, float *g, float *part,
+             float *loss_out);
 
 // Copy one f32 scalar (device to device) -- used to publish the loss.
 void copy_scalar(hipStream_t s, const float *src, float *dst);
-// column sums of g [rows, cols] in the same order as mlp_relu_bwd's
-void mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb);
 // elementwise operators of node-level graphs (outputs may alias inputs)
 void ew_relu(hipStream_t s, int64_t n, const float *x, float *y);                  // y = max(x, 0)
 void ew_add(hipStream_t s, int64_t n, const float *a, const float *b, float *y);   // y = a + b

@@ -8,14 +8,12 @@
 namespace ckpt {
 namespace {
 
-// Workgroup = 64 columns x 4 row groups over a block of 16 rows (blockIdx.y);
-// MASK: dr = g * [z > 0], else the sums are of g itself; the workgroup's
-// column sums over its rows, ((s0 + s1) + s2) + s3 with s_j = rows j, j+4, ..
-// in order, go to pdb[blockIdx.y][cols].
-template <bool MASK>
-__global__ __launch_bounds__(256) void k_mlp_relu_bwd(int rows, int cols, const float *__restrict__ g,
-                                                      const float *__restrict__ z,
-                                                      float *__restrict__ dr, float *__restrict__ pdb) {
+// Workgroup = 64 columns x 4 row groups over a block of 16 rows (blockIdx.y)
+// of g (of g where z > 0 when z is given): the workgroup's column sums over
+// its rows, ((s0 + s1) + s2) + s3 with s_j = rows j, j+4, .. in order, go to
+// pdb[blockIdx.y][cols].
+__global__ __launch_bounds__(256) void k_colsum_part(int rows, int cols, const float *__restrict__ g,
+                                                     const float *__restrict__ z, float *__restrict__ pdb) {
   __shared__ float part[4][64];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + tx, r0 = blockIdx.y * 16 + ty;
@@ -27,17 +25,11 @@ __global__ __launch_bounds__(256) void k_mlp_relu_bwd(int rows, int cols, const 
       const int m = r0 + 4 * i;
       const size_t e = size_t(m < rows ? m : 0) * cols + n;
       gv[i] = g[e];
-      zv[i] = MASK ? z[e] : 0.f;
+      zv[i] = z ? z[e] : 1.f;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int m = r0 + 4 * i;
-      if (m < rows) {
-        const float v = MASK ? (zv[i] > 0.f ? gv[i] : 0.f) : gv[i];
-        if (MASK) dr[size_t(m) * cols + n] = v;
-        s += v;
-      }
-    }
+    for (int i = 0; i < 4; ++i)
+      if (r0 + 4 * i < rows) s += zv[i] > 0.f ? gv[i] : 0.f;
   }
   part[ty][tx] = s;
   __syncthreads();
@@ -63,26 +55,54 @@ __global__ __launch_bounds__(256) void k_colsum_rows(int R, int cols, const floa
   db[n] = s;
 }
 
-// Single block of 1024 threads: thread t sums elements t, t+1024, ...; then a
-// fixed binary tree in LDS.
-__global__ __launch_bounds__(1024) void k_mse_head(int64_t count, const float *__restrict__ y,
-                                                   const float *__restrict__ t, float *__restrict__ g,
-                                                   float *__restrict__ loss_out) {
-  __shared__ float red[1024];
-  const float inv = 1.0f / float(count);
-  float s = 0.f;
-  for (int64_t i = threadIdx.x; i < count; i += 1024) {
-    float d = y[i] - t[i];
-    g[i] = 2.0f * d * inv;
-    s += d * d;
-  }
-  red[threadIdx.x] = s;
+// Sum of 256 values by a fixed binary tree in LDS, in thread 0.
+__device__ __forceinline__ float tree256(float v, float *red) {
+  red[threadIdx.x] = v;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = 128; w > 0; w >>= 1) {
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) loss_out[0] = red[0] * inv;
+  return red[0];
+}
+
+// Each workgroup sums elements 256 b + t, then 256 gridDim.x further, ...;
+// its sum times scale goes to part[b] (2,048 elements per workgroup and up to
+// 256 workgroups: one workgroup alone took 120 us over 262,144 elements, bound
+// by its own loads).
+__global__ __launch_bounds__(256) void k_mse_part(int64_t count, const float *__restrict__ y,
+                                                  const float *__restrict__ t, float *__restrict__ g, float scale,
+                                                  float *__restrict__ part) {
+  __shared__ float red[256];
+  const float inv = 1.0f / float(count);
+  float s = 0.f;
+  const int64_t step = int64_t(gridDim.x) * 256;
+  for (int64_t i0 = blockIdx.x * int64_t(256) + threadIdx.x; i0 < count; i0 += 4 * step) {
+    float yv[4], tv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + u * step < count ? i0 + u * step : i0;
+      yv[u] = y[i];
+      tv[u] = t[i];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i0 + u * step < count) {
+        const float d = yv[u] - tv[u];
+        g[i0 + u * step] = 2.0f * d * inv;
+        s += d * d;
+      }
+  }
+  const float v = tree256(s, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = v * scale;
+}
+
+// out = scale * the sum of n <= 256 values
+__global__ __launch_bounds__(256) void k_sum256(int n, const float *__restrict__ v, float scale,
+                                                float *__restrict__ out) {
+  __shared__ float red[256];
+  const float s = tree256(int(threadIdx.x) < n ? v[threadIdx.x] : 0.f, red);
+  if (threadIdx.x == 0) out[0] = s * scale;
 }
 
 __global__ void k_copy_scalar(const float *src, float *dst) { dst[0] = src[0]; }
@@ -110,20 +130,11 @@ int ew_blocks(int64_t n) {
 
 }  // namespace
 
-int mlp_relu_row_blocks(int rows) { return (rows + 15) / 16; }
+int mlp_row_blocks(int rows) { return (rows + 15) / 16; }
 
-void mlp_relu_bwd(hipStream_t s, int rows, int cols, const float *g, const float *z, float *dr,
-                  float *db, float *pdb) {
-  const int R = mlp_relu_row_blocks(rows);
-  hipLaunchKernelGGL(k_mlp_relu_bwd<true>, dim3((cols + 63) / 64, R), dim3(256), 0, s, rows, cols, g, z,
-                     dr, pdb);
-  hipLaunchKernelGGL(k_colsum_rows, dim3((cols + 255) / 256), dim3(256), 0, s, R, cols, pdb, db);
-}
-
-void mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb) {
-  const int R = mlp_relu_row_blocks(rows);
-  hipLaunchKernelGGL(k_mlp_relu_bwd<false>, dim3((cols + 63) / 64, R), dim3(256), 0, s, rows, cols, g,
-                     nullptr, nullptr, pdb);
+void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb) {
+  const int R = mlp_row_blocks(rows);
+  hipLaunchKernelGGL(k_colsum_part, dim3((cols + 63) / 64, R), dim3(256), 0, s, rows, cols, g, z, pdb);
   hipLaunchKernelGGL(k_colsum_rows, dim3((cols + 255) / 256), dim3(256), 0, s, R, cols, pdb, db);
 }
 
@@ -140,8 +151,22 @@ void ew_copy(hipStream_t s, int64_t n, const float *x, float *y) {
   hipLaunchKernelGGL(k_elementwise<EW_COPY>, dim3(ew_blocks(n)), dim3(256), 0, s, n, x, nullptr, y);
 }
 
-void mse_head(hipStream_t s, int64_t count, const float *y, const float *t, float *g, float *loss_out) {
-  hipLaunchKernelGGL(k_mse_head, dim3(1), dim3(1024), 0, s, count, y, t, g, loss_out);
+int mse_blocks(int64_t count) {
+  const int64_t b = (count + 2047) / 2048;
+  return int(b < 256 ? b : 256);
+}
+
+int mse_head(hipStream_t s, int64_t count, const float *y, const float *t, float *g, float *part,
+             float *loss_out) {
+  const int nb = mse_blocks(count);
+  const float inv = 1.0f / float(count);
+  if (nb == 1) {
+    hipLaunchKernelGGL(k_mse_part, dim3(1), dim3(256), 0, s, count, y, t, g, inv, loss_out);
+    return 1;
+  }
+  hipLaunchKernelGGL(k_mse_part, dim3(nb), dim3(256), 0, s, count, y, t, g, 1.f, part);
+  hipLaunchKernelGGL(k_sum256, dim3(1), dim3(256), 0, s, nb, part, inv, loss_out);
+  return 2;
 }
 
 void copy_scalar(hipStream_t s, const float *src, float *dst) {

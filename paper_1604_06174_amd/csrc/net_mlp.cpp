@@ -3,7 +3,8 @@
 // that a deep chain stays trainable); head = mean squared error.
 //
 // Static layout per unit: boundary b = [B, D] f32; saved internals a = the
-// pre-activation z [B, D]; gradient scratch q = the masked gradient dr [B, D].
+// pre-activation z [B, D]; gradient scratch q = one [B, D] tensor (the masked
+// gradient dr, which the backward forms as it reads g and z).
 #include "kernels.h"
 #include "net.h"
 
@@ -28,8 +29,8 @@ class MlpNet : public Net {
       wi.push_back(add_param("u" + std::to_string(i) + ".W", uint64_t(D) * D));
       bi.push_back(add_param("u" + std::to_string(i) + ".b", uint64_t(D)));
     }
-    // loss scalar | bias-gradient partial sums of the ReLU backward
-    ks_bytes = 256 + align256(uint64_t(mlp_relu_row_blocks(B)) * D * 4);
+    // loss scalar | partial sums (of the loss, or of a bias gradient)
+    ks_bytes = 256 + align256(uint64_t(mlp_row_blocks(B)) * D * 4);
     timed_family = "k_gemm_f32";
   }
 
@@ -49,32 +50,24 @@ class MlpNet : public Net {
     c.launches += 1;
   }
 
+  float *partials(StepCtx &c) const { return reinterpret_cast<float *>(c.ks + 256); }
+
+  // one launch: dW = x^T dr ([D_in, D_out] = [D, B] x [B, D]), dx = g + dr W^T
+  // and db, with dr = g [z > 0] formed as it is read
   void bwd(int32_t i, const void *g, void *dx, const void *x, const void *, const void *saved,
-           void *q, StepCtx &c) override {
-    const float *gp = static_cast<const float *>(g);
-    float *dr = static_cast<float *>(q);
-    mlp_relu_bwd(c.s, B, D, gp, static_cast<const float *>(saved), dr, G(c, bi[i]),
-                 reinterpret_cast<float *>(c.ks + 256));
-    // dW = x^T dr : [D_in, D_out] = [D, B] x [B, D]
+           void *, StepCtx &c) override {
     timer.begin(c.s);
-    gemm_f32(c.s, D, D, B, static_cast<const float *>(x), D, true, dr, D, false, G(c, wi[i]), D,
-             GEMM_EPI_STORE);
-    timer.end(c.s, gf(D, D, B), gb(D, D, B, 0));
-    c.launches += 3;
-    if (dx) {  // dx = g + dr W^T
-      timer.begin(c.s);
-      gemm_f32(c.s, B, D, D, dr, D, false, P(c, wi[i]), D, true, static_cast<float *>(dx), D,
-               GEMM_EPI_ADD, gp, D);
-      timer.end(c.s, gf(B, D, D), gb(B, D, D, 4.0 * B * D));
-      c.launches += 1;
-    }
+    c.launches += mlp_bwd(c.s, B, D, static_cast<const float *>(g), static_cast<const float *>(saved),
+                          static_cast<const float *>(x), P(c, wi[i]), static_cast<float *>(dx), G(c, wi[i]),
+                          G(c, bi[i]), partials(c));
+    const double two = dx ? 2 : 1;
+    timer.end(c.s, two * gf(B, D, D), two * gb(B, D, D, 4.0 * B * D));
   }
 
   void head(const void *xn, void *g, StepCtx &c) override {
-    mse_head(c.s, int64_t(B) * D, static_cast<const float *>(xn),
-             static_cast<const float *>(c.target), static_cast<float *>(g),
-             reinterpret_cast<float *>(c.ks));
-    c.launches += 1;
+    c.launches += mse_head(c.s, int64_t(B) * D, static_cast<const float *>(xn),
+                           static_cast<const float *>(c.target), static_cast<float *>(g), partials(c),
+                           reinterpret_cast<float *>(c.ks));
   }
 
   // Node graph: 0 data; block i: 1 + 3i fully connected (x W + b), 2 + 3i ReLU,
@@ -113,7 +106,7 @@ class MlpNet : public Net {
         fail(CKPT_E_HIP, "train_step_graph: input copy failed");
     } else if (v == 3 * n + 1) {
       mse_head(c.s, t, static_cast<const float *>(ins[0]), static_cast<const float *>(c.target), y,
-               reinterpret_cast<float *>(c.ks));
+               partials(c), reinterpret_cast<float *>(c.ks));
     } else {
       const int i = (v - 1) / 3, k = (v - 1) % 3;
       const float *x = static_cast<const float *>(ins[0]);
@@ -144,15 +137,10 @@ class MlpNet : public Net {
     }
     const int i = (v - 1) / 3, k = (v - 1) % 3;
     if (k == 0) {  // fully connected: dx = dy W^T, dW = x^T dy, db = column sums of dy
-      const float *x = static_cast<const float *>(ins[0]);
       timer.begin(c.s);
-      gemm_f32(c.s, B, D, D, dy, D, false, P(c, wi[i]), D, true, o, D, GEMM_EPI_STORE);
-      timer.end(c.s, gf(B, D, D), gb(B, D, D, 0));
-      timer.begin(c.s);
-      gemm_f32(c.s, D, D, B, x, D, true, dy, D, false, G(c, wi[i]), D, GEMM_EPI_STORE);
-      timer.end(c.s, gf(D, D, B), gb(D, D, B, 0));
-      mlp_colsum(c.s, B, D, dy, G(c, bi[i]), reinterpret_cast<float *>(c.ks + 256));
-      c.launches += 4;
+      c.launches += mlp_bwd(c.s, B, D, dy, nullptr, static_cast<const float *>(ins[0]), P(c, wi[i]), o, G(c, wi[i]),
+                            G(c, bi[i]), partials(c));
+      timer.end(c.s, 2 * gf(B, D, D), gb(B, D, D, 0) + gb(D, D, B, 0));
     } else if (k == 1) {  // ReLU: the mask from its output
       ew_relu_bwd(c.s, t, dy, static_cast<const float *>(yv), o);
       c.launches += 1;

@@ -147,7 +147,7 @@ class ResNetBasic : public Net {
     ks_dlog = take(4ull * N * K);
     ks_lossn = take(4ull * N);
     ks_nst = take(nst_bytes);                                   // node graph: BN statistics
-    ks_fcpart = take(4ull * mlp_relu_row_blocks(N) * K);         // node graph: FC bias sums
+    ks_fcpart = take(4ull * mlp_row_blocks(N) * K);         // node graph: FC bias sums
     // every unit's batch-norm statistics (mean | rstd per BN, 256-byte
     // aligned), formed by its first forward of the step and read by its
     // re-runs and its backward: held for the whole step, so they are fixed
