@@ -333,8 +333,9 @@ __device__ __forceinline__ u32x4 gatherB_wdgrad(const Args &p, int k, int n, int
   return masked16(p.B + (size_t(co) * p.R * p.R + tap) * p.N + n, (k < kend) & (n < p.N));
 }
 
-// STG (direct loop only): the number of LDS stages, 2 to 5; 0 chooses three
-// where two workgroups then still fit a compute unit's LDS, else two
+// STG (direct loop only): the number of LDS stages, 2 to 5, or 1 for a k range
+// of one slice; 0 chooses three where two workgroups then still fit a compute
+// unit's LDS, else two
 template <int BM, int BN, int WM, int WN, bool AK, bool BK, typename TA, int EPI, int GA, int GB, bool SAFE,
           int STG = 0>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
@@ -469,11 +470,11 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
     // stages: more slices in flight hide more of the load latency, fewer
     // leave LDS for a second workgroup per compute unit
     constexpr int NS = STG ? STG : (direct_three_stages(BM, BN, EPI_SCR) ? 3 : 2);
-    static_assert(NS >= 2 && NS <= 5, "two to five stages");
+    static_assert(NS >= 1 && NS <= 5, "one to five stages");
     static_assert((NS - 2) * (PA + PB) <= 63, "loads in flight fit the vector-memory counter");
-    __shared__ __align__(1024) unsigned char sa0[SZA1], sa1[SZA1], sa2[NS > 2 ? SZA1 : 1],
+    __shared__ __align__(1024) unsigned char sa0[SZA1], sa1[NS > 1 ? SZA1 : 1], sa2[NS > 2 ? SZA1 : 1],
         sa3[NS > 3 ? SZA1 : 1], sa4[NS > 4 ? SZA1 : 1];
-    __shared__ __align__(1024) unsigned char sb0[SZB1], sb1[SZB1], sb2[NS > 2 ? SZB1 : 1],
+    __shared__ __align__(1024) unsigned char sb0[SZB1], sb1[NS > 1 ? SZB1 : 1], sb2[NS > 2 ? SZB1 : 1],
         sb3[NS > 3 ? SZB1 : 1], sb4[NS > 4 ? SZB1 : 1];
     __shared__ __align__(16) unsigned char sepi[EPI_SCR <= SZA1 ? 1 : EPI_SCR];
     if constexpr (EPI_SCR <= SZA1) scr = sa0;
@@ -621,19 +622,26 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
     // visible and tells that every wavefront is done with slice kt - 1, whose
     // stage then takes slice kt + NS - 1.  (A bare s_barrier: __syncthreads'
     // fence would wait for every load in flight.)
-    unroll<NS - 1>([&](auto J) { issue(decltype(J)::value, stage_a(J), stage_b(J)); });
-    auto step = [&](int kt, auto J) {
-      constexpr int w = (decltype(J)::value + NS - 1) % NS;
-      __builtin_amdgcn_s_waitcnt(vmcnt_le_lds0((NS - 2) * (PA + PB)));
+    if constexpr (NS == 1) {  // a single slice
+      issue(0, sa0, sb0);
+      __builtin_amdgcn_s_waitcnt(vmcnt_le(0));
       __builtin_amdgcn_s_barrier();
-      issue(kt + NS - 1, stage_a(std::integral_constant<int, w>{}), stage_b(std::integral_constant<int, w>{}));
-      compute(stage_a(J), stage_b(J));
-    };
-    int kt = 0;
-    for (; kt + NS <= nk; kt += NS) unroll<NS>([&](auto J) { step(kt + decltype(J)::value, J); });
-    unroll<NS - 1>([&](auto J) {
-      if (kt + decltype(J)::value < nk) step(kt + decltype(J)::value, J);
-    });
+      if (nk > 0) compute(sa0, sb0);
+    } else {
+      unroll<NS - 1>([&](auto J) { issue(decltype(J)::value, stage_a(J), stage_b(J)); });
+      auto step = [&](int kt, auto J) {
+        constexpr int w = (decltype(J)::value + NS - 1) % NS;
+        __builtin_amdgcn_s_waitcnt(vmcnt_le_lds0((NS - 2) * (PA + PB)));
+        __builtin_amdgcn_s_barrier();
+        issue(kt + NS - 1, stage_a(std::integral_constant<int, w>{}), stage_b(std::integral_constant<int, w>{}));
+        compute(stage_a(J), stage_b(J));
+      };
+      int kt = 0;
+      for (; kt + NS <= nk; kt += NS) unroll<NS>([&](auto J) { step(kt + decltype(J)::value, J); });
+      unroll<NS - 1>([&](auto J) {
+        if (kt + decltype(J)::value < nk) step(kt + decltype(J)::value, J);
+      });
+    }
     // every load (the re-reads past the range included) has landed and every
     // wavefront is done with the stages before the epilogue reuses them
     __builtin_amdgcn_s_waitcnt(vmcnt_le(0));
@@ -1124,6 +1132,16 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BK, typename TA, int GA,
 void launch_epi(const Args &a, int epi, int splits, hipStream_t s) {
   constexpr bool direct = SAFE && std::is_same<TA, __bf16>::value;
   constexpr int scr = cmax(WM * WN * 16 * (BN / WN) * 4, 4 * 2 * BN * 8 * 4);  // a bound on any epilogue's scratch
+  // a k range of one slice (the expansions of 64 channels) needs one stage: half
+  // the LDS, so four workgroups share a compute unit instead of two.  Their time
+  // is latency (loads, barriers, stores), not work: 100,352 x 256 x 64 with its
+  // statistics took 32.8 us with two, 29.3 with four.
+  if constexpr (direct && BM == 128 && BN == 128 && WM * WN == 4 && GA == G_DENSE && GB == G_DENSE) {
+    if (a.kper <= KS) {
+      launch_epi_s<BM, BN, WM, WN, AK, BK, TA, GA, GB, SAFE, 1>(a, epi, splits, s);
+      return;
+    }
+  }
   if constexpr (direct && !direct_three_stages(BM, BN, scr)) {
     const long tiles = long((a.N + BN - 1) / BN) * ((a.M + BM - 1) / BM) * splits;
     if (tiles <= 256) {
