@@ -122,25 +122,23 @@ __device__ __forceinline__ void finalize_channel(int j, int J, double sa, double
   }
 }
 
-template <bool FWD, bool CM>
+// Channel-major partials: a workgroup per channel.
+template <bool FWD>
 __global__ __launch_bounds__(256) void k_bn_finalize(const double *__restrict__ part, int nb, int J,
                                                      double m, float *__restrict__ out,
                                                      float *__restrict__ dgamma,
                                                      float *__restrict__ dbeta) {
   __shared__ double r0[4], r1[4];
   const int j = blockIdx.x;
-  // element k of sum w at p_w[k * step]
-  const double *p0 = CM ? part + size_t(j) * nb : part + j;
-  const double *p1 = CM ? part + (size_t(J) + j) * nb : part + J + j;
-  const size_t step = CM ? 1 : size_t(2) * J;
+  const double *p0 = part + size_t(j) * nb, *p1 = part + (size_t(J) + j) * nb;
   double a = 0, b = 0;
   int k = threadIdx.x;
   for (; k + 3 * 256 < nb; k += 4 * 256) {  // four partials of each sum in flight
     double ta[4], tb[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      ta[u] = p0[(k + 256 * u) * step];
-      tb[u] = p1[(k + 256 * u) * step];
+      ta[u] = p0[k + 256 * u];
+      tb[u] = p1[k + 256 * u];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -149,8 +147,8 @@ __global__ __launch_bounds__(256) void k_bn_finalize(const double *__restrict__ 
     }
   }
   for (; k < nb; k += 256) {
-    a += p0[k * step];
-    b += p1[k * step];
+    a += p0[k];
+    b += p1[k];
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -168,45 +166,52 @@ __global__ __launch_bounds__(256) void k_bn_finalize(const double *__restrict__ 
                           out, dgamma, dbeta);
 }
 
-// Block-major partials of many channels: a workgroup takes 16 consecutive
-// channels (16 lanes read 128 contiguous bytes per partial) and splits the nb
-// partials into 16 slices; slice s adds k = s, s + 16, ... in turn (eight
-// loads in flight), and the 16 slice sums of a channel are added in slice
-// order.
+// Block-major partials: a workgroup takes 8 consecutive channels (8 lanes read
+// 64 contiguous bytes of a partial's row) and splits the nb rows into 128
+// slices, slice s adding rows s, s + 128, ... in order, all its loads of up to
+// four rounds in flight; the slices combine by a butterfly over the 8 of a
+// wavefront, then in wavefront order.  Its time is a launch and one or two load
+// latencies: with a workgroup per channel (8-byte loads from rows 2 J apart)
+// 784 rows of 256 channels took 7.0 us, with 16 slices per 16 channels 516 rows
+// of 512 channels 6.6; 5.7 and 4.3 so.
 template <bool FWD>
-__global__ __launch_bounds__(256) void k_bn_finalize_wide(const double *__restrict__ part, int nb, int J,
-                                                          double m, float *__restrict__ out,
-                                                          float *__restrict__ dgamma,
-                                                          float *__restrict__ dbeta) {
-  __shared__ double r0[16][17], r1[16][17];
-  const int cl = threadIdx.x % 16, sl = threadIdx.x / 16;
-  const int j = blockIdx.x * 16 + cl;
+__global__ __launch_bounds__(1024) void k_bn_finalize_rows(const double *__restrict__ part, int nb, int J,
+                                                           double m, float *__restrict__ out,
+                                                           float *__restrict__ dgamma,
+                                                           float *__restrict__ dbeta) {
+  __shared__ double r0[16][8], r1[16][8];
+  const int cl = threadIdx.x % 8, sl = threadIdx.x / 8;
+  const int j = blockIdx.x * 8 + cl;
   double a = 0, b = 0;
-  if (j < J) {
-    int k = sl;
-    for (; k + 7 * 16 < nb; k += 8 * 16) {
-      double ta[8], tb[8];
+  if (j < J)
+    for (int k0 = sl; k0 < nb; k0 += 4 * 128) {
+      double ta[4], tb[4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        ta[u] = part[(size_t(k + 16 * u) * 2 + 0) * J + j];
-        tb[u] = part[(size_t(k + 16 * u) * 2 + 1) * J + j];
+      for (int u = 0; u < 4; ++u) {
+        const bool in = k0 + 128 * u < nb;
+        const double *row = part + size_t(in ? k0 + 128 * u : k0) * 2 * J + j;
+        ta[u] = in ? row[0] : 0.0;
+        tb[u] = in ? row[J] : 0.0;
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < 4; ++u) {
         a += ta[u];
         b += tb[u];
       }
     }
-    for (; k < nb; k += 16) {
-      a += part[(size_t(k) * 2 + 0) * J + j];
-      b += part[(size_t(k) * 2 + 1) * J + j];
-    }
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) {
+    a += __shfl_xor(a, off);
+    b += __shfl_xor(b, off);
   }
-  r0[sl][cl] = a;
-  r1[sl][cl] = b;
+  if ((threadIdx.x & 63) < 8) {
+    r0[threadIdx.x >> 6][cl] = a;
+    r1[threadIdx.x >> 6][cl] = b;
+  }
   __syncthreads();
-  if (sl == 0 && j < J) {
+  if (threadIdx.x < 8 && j < J) {
     double sa = 0, sb = 0;
+#pragma unroll
     for (int t = 0; t < 16; ++t) {
       sa += r0[t][cl];
       sb += r1[t][cl];
@@ -643,33 +648,22 @@ static int64_t bn_pb(int64_t P, int J) {
   return (P + nb - 1) / nb;
 }
 
-// block-major partials of this many channels or more take the tiled finalize
-constexpr int BN_WIDE_J = 512;
-
 void bn_finalize_fwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *st,
                      bool channel_major) {
-  if (!channel_major && J >= BN_WIDE_J)
-    hipLaunchKernelGGL((k_bn_finalize_wide<true>), dim3((J + 15) / 16), dim3(256), 0, s, part, nb, J,
-                       double(m), st, nullptr, nullptr);
-  else if (channel_major)
-    hipLaunchKernelGGL((k_bn_finalize<true, true>), dim3(J), dim3(256), 0, s, part, nb, J, double(m),
-                       st, nullptr, nullptr);
+  if (channel_major)
+    hipLaunchKernelGGL(k_bn_finalize<true>, dim3(J), dim3(256), 0, s, part, nb, J, double(m), st, nullptr, nullptr);
   else
-    hipLaunchKernelGGL((k_bn_finalize<true, false>), dim3(J), dim3(256), 0, s, part, nb, J, double(m),
-                       st, nullptr, nullptr);
+    hipLaunchKernelGGL(k_bn_finalize_rows<true>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), st,
+                       nullptr, nullptr);
 }
 
 void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *sums,
                      float *dgamma, float *dbeta, bool channel_major) {
-  if (!channel_major && J >= BN_WIDE_J)
-    hipLaunchKernelGGL((k_bn_finalize_wide<false>), dim3((J + 15) / 16), dim3(256), 0, s, part, nb, J,
-                       double(m), sums, dgamma, dbeta);
-  else if (channel_major)
-    hipLaunchKernelGGL((k_bn_finalize<false, true>), dim3(J), dim3(256), 0, s, part, nb, J, double(m),
-                       sums, dgamma, dbeta);
+  if (channel_major)
+    hipLaunchKernelGGL(k_bn_finalize<false>, dim3(J), dim3(256), 0, s, part, nb, J, double(m), sums, dgamma, dbeta);
   else
-    hipLaunchKernelGGL((k_bn_finalize<false, false>), dim3(J), dim3(256), 0, s, part, nb, J, double(m),
-                       sums, dgamma, dbeta);
+    hipLaunchKernelGGL(k_bn_finalize_rows<false>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), sums,
+                       dgamma, dbeta);
 }
 
 void bn_apply(hipStream_t s, int res, int64_t P, int J, const float *Cv, const float *st,
