@@ -28,7 +28,14 @@
 //             offset are the same for the whole workgroup, and a chunk's
 //             source is its row's fixed address plus that offset, or zero
 //             when the tap is outside the image (a per-row mask of taps)
-//             (direct loop only)
+//             (direct loop only).  With STG >= 8 the rows are not gathered per
+//             tap at all (HALO, 3x3, stride 1, padding 1): the pixels that a
+//             tile's rows reach through any tap are consecutive in memory, BM +
+//             2 W + 2 of them, so they are loaded into LDS once with all their
+//             channels and each tap's operands are read from there, W kh + kw
+//             pixels further on (zeros from a zero row outside the image); only
+//             the weights pass through the ring.  A tile then loads 1.2 - 2.3
+//             times its own rows instead of nine times
 // Out-of-image taps read zero.
 //
 // Block = 4 or 8 wavefronts (256 or 512 threads) in a WM x WN grid; each wavefront owns a
@@ -56,6 +63,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -80,6 +88,11 @@ constexpr bool direct_three_stages(int BM, int BN, int epi_scratch) {
 
 constexpr int KS = 64;      // k per LDS slice: two 32-deep MFMA steps
 constexpr int KP = KS + 8;  // padded row (bf16 elements): 144-byte rows
+
+// LDS for a tile's halo and zero row (rows rounded up to whole load
+// instructions).  Two workgroups then fit a compute unit, but for 128 x 128 and
+// 64 x 64 tiles of eight wavefronts, which run when there are too few for that.
+constexpr int halo_bytes(int BM, int waves) { return (BM == 64 && waves == 8 ? 84 : 48) * 1024; }
 
 enum { G_DENSE = 0, GA_FWD = 1, GA_DGRAD = 2, GB_WGRAD = 3, GB_WDGRAD = 4, GA_CAT = 5, GA_FWDT = 6,
        GA_DGRADT = 7 };
@@ -335,7 +348,7 @@ __device__ __forceinline__ u32x4 gatherB_wdgrad(const Args &p, int k, int n, int
 
 // STG (direct loop only): the number of LDS stages, 2 to 5, or 1 for a k range
 // of one slice; 0 chooses three where two workgroups then still fit a compute
-// unit's LDS, else two
+// unit's LDS, else two; + 8: A from a halo (see above)
 template <int BM, int BN, int WM, int WN, bool AK, bool BK, typename TA, int EPI, int GA, int GB, bool SAFE,
           int STG = 0>
 __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
@@ -415,15 +428,32 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
       ctap[c] = col_tap(p, n0 + (e % (BN / 8)) * 8);
     }
   }
+  constexpr bool HALO = (STG & 8) != 0;
+  constexpr int HALO_BYTES = HALO ? halo_bytes(BM, WM * WN) : 1;
+  static_assert(!HALO || ((GA == GA_FWDT || GA == GA_DGRADT) && DIRECT), "the halo serves the tap-uniform gathers");
   // GA_FWDT / GA_DGRADT: per chunk (of the direct loop's layout), the byte
   // address of its source at tap (0, 0) (an integer: the pixel may lie
   // outside the image) and the mask of taps inside the image (zero for a
   // row past M)
   constexpr bool GAT = GA == GA_FWDT || GA == GA_DGRADT;
   static_assert(!GAT || DIRECT, "the tap-uniform gathers run in the direct loop");
-  uint64_t tsrc[GAT ? PA : 1];
-  uint32_t tmask[GAT ? PA : 1];
-  if constexpr (GAT) {
+  uint64_t tsrc[GAT && !HALO ? PA : 1];
+  uint32_t tmask[GAT && !HALO ? PA : 1];
+  // HALO: per operand row of the lane, the mask of taps inside the image
+  uint32_t hmask[HALO ? TM : 1];
+  if constexpr (HALO) {
+#pragma unroll
+    for (int a = 0; a < TM; ++a) {
+      const RowPix rp = row_pixel(p, m0 + wm + a * 16 + i16, p.H, p.W);
+      uint32_t mk = 0;
+      for (int t = 0; t < 9; ++t) {
+        const int dy = GA == GA_FWDT ? t / 3 - 1 : 1 - t / 3, dx = GA == GA_FWDT ? t % 3 - 1 : 1 - t % 3;
+        const int y = rp.y + dy, x = rp.x + dx;
+        mk |= uint32_t((y >= 0) & (y < p.H) & (x >= 0) & (x < p.W)) << t;
+      }
+      hmask[a] = rp.ok ? mk : 0u;
+    }
+  } else if constexpr (GAT) {
     const int C = 1 << p.cshift;
 #pragma unroll
     for (int c = 0; c < PA; ++c) {
@@ -466,19 +496,39 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
     //   k-major operand: [k][rows / 8 chunks of 8 rows], the chunk of
     //     logical row-group g stored in slot g ^ (2 (k & 3) mod chunks per
     //     row).
-    constexpr int SZA1 = BM * KS * 2, SZB1 = BN * KS * 2;
+    constexpr int SZA1 = HALO ? 16 : BM * KS * 2, SZB1 = BN * KS * 2;
+    constexpr int STGN = STG & 7, PAL = HALO ? 0 : PA;  // loads of A per slice
     // stages: more slices in flight hide more of the load latency, fewer
     // leave LDS for a second workgroup per compute unit
-    constexpr int NS = STG ? STG : (direct_three_stages(BM, BN, EPI_SCR) ? 3 : 2);
+    constexpr int NS = STGN ? STGN : (direct_three_stages(BM, BN, EPI_SCR) ? 3 : 2);
     static_assert(NS >= 1 && NS <= 5, "one to five stages");
-    static_assert((NS - 2) * (PA + PB) <= 63, "loads in flight fit the vector-memory counter");
+    static_assert((NS - 2) * (PAL + PB) <= 63, "loads in flight fit the vector-memory counter");
     __shared__ __align__(1024) unsigned char sa0[SZA1], sa1[NS > 1 ? SZA1 : 1], sa2[NS > 2 ? SZA1 : 1],
         sa3[NS > 3 ? SZA1 : 1], sa4[NS > 4 ? SZA1 : 1];
     __shared__ __align__(1024) unsigned char sb0[SZB1], sb1[NS > 1 ? SZB1 : 1], sb2[NS > 2 ? SZB1 : 1],
         sb3[NS > 3 ? SZB1 : 1], sb4[NS > 4 ? SZB1 : 1];
-    __shared__ __align__(16) unsigned char sepi[EPI_SCR <= SZA1 ? 1 : EPI_SCR];
-    if constexpr (EPI_SCR <= SZA1) scr = sa0;
+    __shared__ __align__(1024) unsigned char halo[HALO_BYTES];
+    static_assert(!HALO || EPI_SCR <= HALO_BYTES, "the epilogue's scratch takes the halo's place");
+    __shared__ __align__(16) unsigned char sepi[HALO || EPI_SCR <= SZA1 ? 1 : EPI_SCR];
+    if constexpr (HALO) scr = halo;
+    else if constexpr (EPI_SCR <= SZA1) scr = sa0;
     else scr = sepi;
+    // halo layout: pixel m0 - W - 1 + i in row i, its chunk c (8 channels) in
+    // slot c ^ (i mod 16) (mod 8 with 64 channels); then a row of zeros
+    const int hpitch = (1 << p.cshift) * 2, hrows = BM + 2 * p.W + 2;
+    const int hsw = min(hpitch / 16, 16) - 1;
+    if constexpr (HALO) {
+      const int cl = p.cshift - 3;  // log2 chunks per row
+      const int64_t first = int64_t(m0) - p.W - 1;
+      const int total = hrows << cl;
+      for (int e = tid; e - lane < total; e += NT) {
+        // (a lane past the last row re-reads it into the rows behind, which are
+        // the zero row's or unused and written after)
+        const int i = min(e >> cl, hrows - 1), c = (e & ((1 << cl) - 1)) ^ (i & hsw);
+        const int64_t px = min(max(first + i, int64_t(0)), int64_t(p.M) - 1);
+        load_lds16(reinterpret_cast<const __bf16 *>(A) + (px << p.cshift) + c * 8, halo + (e - lane) * 16);
+      }
+    }
     // stage i's arrays (i a compile-time constant: each stage is its own
     // object, so the compiler knows which loads an LDS read waits for)
     auto stage_a = [&](auto I) -> unsigned char * {
@@ -517,7 +567,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
       // byte offset of its source from tap (0, 0)'s (workgroup-uniform)
       uint32_t tbit = 0;
       int64_t toff = 0;
-      if constexpr (GAT) {
+      if constexpr (GAT && !HALO) {
         const int tap = k0 >> p.cshift, ch0 = k0 & ((1 << p.cshift) - 1);
         int kh, kw;
         tap_hw(tap, p, kh, kw);
@@ -526,7 +576,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
         toff = (px * (int64_t(1) << p.cshift) + ch0) * 2;
       }
 #pragma unroll
-      for (int c = 0; c < PA; ++c) {
+      for (int c = 0; c < PAL; ++c) {
         const int e = c * NT + tid;
         const void *src;
         if (AK) {
@@ -578,13 +628,31 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
       }
     };
     // one k step of 32 from stage (sa, sb): the MFMA operands, swizzled back
-    auto compute = [&](const unsigned char *sa, const unsigned char *sb) {
+    // (A of slice kt from the halo)
+    auto compute = [&](int kt, const unsigned char *sa, const unsigned char *sb) {
+      int hrow[HALO ? TM : 1], hx[HALO ? TM : 1], hc = 0;
+      if constexpr (HALO) {
+        const int k0 = kslice(kt), tap = k0 >> p.cshift;
+        int kh, kw;
+        tap_hw(tap, p, kh, kw);
+        const int shift = GA == GA_FWDT ? kh * p.W + kw : (2 - kh) * p.W + 2 - kw;
+        hc = ((k0 & ((1 << p.cshift) - 1)) >> 3) + q;
+#pragma unroll
+        for (int a = 0; a < TM; ++a) {
+          const bool in = (hmask[a] >> tap) & 1;
+          const int i = in ? wm + a * 16 + i16 + shift : hrows;
+          hrow[a] = i * hpitch;
+          hx[a] = in ? i & hsw : 0;
+        }
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ks += 32) {
         bf16x8 av[TM], bv[TN];
 #pragma unroll
         for (int a = 0; a < TM; ++a) {
-          if constexpr (AK) {
+          if constexpr (HALO) {
+            av[a] = *reinterpret_cast<const bf16x8 *>(halo + hrow[a] + ((hc + (ks >> 3)) ^ hx[a]) * 16);
+          } else if constexpr (AK) {
             const int r = wm + a * 16 + i16, g = ((ks >> 3) + q) ^ (r & 7);
             av[a] = *reinterpret_cast<const bf16x8 *>(sa + (r * 8 + g) * 16);
           } else {
@@ -622,19 +690,27 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_bf16(Args p) {
     // visible and tells that every wavefront is done with slice kt - 1, whose
     // stage then takes slice kt + NS - 1.  (A bare s_barrier: __syncthreads'
     // fence would wait for every load in flight.)
+    if constexpr (HALO) {
+      // the zero row, once every load into the halo has landed (a wavefront's own
+      // loads may spill past the last row); the first slice's barrier shows it
+      __builtin_amdgcn_s_waitcnt(vmcnt_le(0));
+      __builtin_amdgcn_s_barrier();
+      for (int e = tid; e < hpitch / 16; e += NT)
+        *reinterpret_cast<u32x4 *>(halo + hrows * hpitch + e * 16) = zero_chunk();
+    }
     if constexpr (NS == 1) {  // a single slice
       issue(0, sa0, sb0);
       __builtin_amdgcn_s_waitcnt(vmcnt_le(0));
       __builtin_amdgcn_s_barrier();
-      if (nk > 0) compute(sa0, sb0);
+      if (nk > 0) compute(0, sa0, sb0);
     } else {
       unroll<NS - 1>([&](auto J) { issue(decltype(J)::value, stage_a(J), stage_b(J)); });
       auto step = [&](int kt, auto J) {
         constexpr int w = (decltype(J)::value + NS - 1) % NS;
-        __builtin_amdgcn_s_waitcnt(vmcnt_le_lds0((NS - 2) * (PA + PB)));
+        __builtin_amdgcn_s_waitcnt(vmcnt_le_lds0((NS - 2) * (PAL + PB)));
         __builtin_amdgcn_s_barrier();
         issue(kt + NS - 1, stage_a(std::integral_constant<int, w>{}), stage_b(std::integral_constant<int, w>{}));
-        compute(stage_a(J), stage_b(J));
+        compute(kt, stage_a(J), stage_b(J));
       };
       int kt = 0;
       for (; kt + NS <= nk; kt += NS) unroll<NS>([&](auto J) { step(kt + decltype(J)::value, J); });
@@ -1132,6 +1208,21 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BK, typename TA, int GA,
 void launch_epi(const Args &a, int epi, int splits, hipStream_t s) {
   constexpr bool direct = SAFE && std::is_same<TA, __bf16>::value;
   constexpr int scr = cmax(WM * WN * 16 * (BN / WN) * 4, 4 * 2 * BN * 8 * 4);  // a bound on any epilogue's scratch
+  // 3x3 convolutions of stride 1 whose halo fits: tiles of 128 or 256 rows
+  // (forward / data gradient with its sums, batch 32: 56 x 56 x 64 22.1 / 28.1 us
+  // gathered, 21.0 / 24.8 from a halo; 28 x 28 x 128 17.2 / 23.1 and 16.3 /
+  // 21.5), and the forward of 64 x 64 tiles with eight wavefronts (7 x 7 x 512
+  // 24.4 and 23.4).  The other 64-row tiles are bound by their operand reads and
+  // barriers, not by loads: 14 x 14 x 256 forward 19.5 both ways, the data
+  // gradients of 14 x 14 and 7 x 7 23.4 and 28.5 gathered, 24.1 and 32.5 so.
+  if constexpr (direct && (GA == GA_FWDT || GA == GA_DGRADT) &&
+                (BM >= 128 || (GA == GA_FWDT && BM == 64 && WM * WN == 8))) {
+    if (a.R == 3 && a.S == 1 && a.P == 1 && a.H == a.Ho && a.W == a.Wo && splits == 1 &&
+        (int64_t(BM + 2 * a.W + 2) << (a.cshift + 1)) + std::max(1024, 2 << a.cshift) <= halo_bytes(BM, WM * WN)) {
+      launch_epi_s<BM, BN, WM, WN, AK, BK, TA, GA, GB, SAFE, BM + BN == 256 && WM * WN == 4 ? 8 + 2 : 8 + 3>(a, epi, splits, s);
+      return;
+    }
+  }
   // a k range of one slice (the expansions of 64 channels) needs one stage: half
   // the LDS, so four workgroups share a compute unit instead of two.  Their time
   // is latency (loads, barriers, stores), not work: 100,352 x 256 x 64 with its
