@@ -215,26 +215,36 @@ __global__ __launch_bounds__(256) void k_im2col7(int N, int H, int W, int Ho, in
   }
 }
 
-// The same patches in rows of KP >= 147 elements (KP a multiple of 8), the
-// columns past 147 zero: one 16-byte chunk of a row per thread.
+// Padded rows: each thread writes 16-byte chunks of a patch row.  Workgroup =
+// up to 64 output pixels of one output row: the 7 input rows they touch go to
+// LDS once (zeros outside the image), where a patch row's part for a kernel row
+// is 21 consecutive values.  Bound by the stores (128 MB at batch 32, 224 x
+// 224); with each value fetched from memory by itself, its position found by
+// 64-bit divisions, that took 80 us, 51 so.
+constexpr int IC_WO = 64, IC_ROW = (2 * (IC_WO - 1) + 7) * 3;
 __global__ __launch_bounds__(256) void k_im2col7p(int N, int H, int W, int Ho, int Wo, int KP,
                                                   const __bf16 *__restrict__ X, __bf16 *__restrict__ col) {
+  __shared__ __bf16 rows[7][IC_ROW + 1];
+  const int ho = blockIdx.x % Ho, n = blockIdx.x / Ho, wo0 = blockIdx.y * IC_WO;
+  const int nw = min(IC_WO, Wo - wo0);
+  const int first = (2 * wo0 - 3) * 3;  // the tile's first value within an input row
+  for (int e = threadIdx.x; e < 7 * IC_ROW; e += 256) {
+    const int kh = e / IC_ROW, o = e % IC_ROW, hi = 2 * ho + kh - 3, wi = first + o;
+    const bool ok = hi >= 0 && hi < H && wi >= 0 && wi < 3 * W;
+    rows[kh][o] = ok ? X[(int64_t(n) * H + hi) * W * 3 + wi] : (__bf16)0.f;
+  }
+  __syncthreads();
   const int CH = KP / 8;
-  const int64_t total = int64_t(N) * Ho * Wo * CH;
-  for (int64_t e = blockIdx.x * int64_t(256) + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
-    const int j = int(e % CH);
-    const int64_t m = e / CH;
-    const int wo = int(m % Wo), ho = int((m / Wo) % Ho), n = int(m / (int64_t(Wo) * Ho));
+  __bf16 *dst = col + (int64_t(blockIdx.x) * Wo + wo0) * KP;
+  for (int e = threadIdx.x; e < nw * CH; e += 256) {
+    const int wo = e / CH, k0 = e % CH * 8;
     bf16x8 v;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int k = j * 8 + u;
-      const int ci = k % 3, t = k / 3, kh = t / 7, kw = t % 7;
-      const int hi = 2 * ho + kh - 3, wi = 2 * wo + kw - 3;
-      v[u] = (k < 147 && hi >= 0 && hi < H && wi >= 0 && wi < W) ? X[((int64_t(n) * H + hi) * W + wi) * 3 + ci]
-                                                                : (__bf16)0.f;
+      const int k = k0 + u, kh = k / 21;
+      v[u] = k < 147 ? rows[kh][6 * wo + k - 21 * kh] : (__bf16)0.f;
     }
-    *reinterpret_cast<bf16x8 *>(col + m * KP + j * 8) = v;
+    *reinterpret_cast<bf16x8 *>(dst + int64_t(wo) * KP + k0) = v;
   }
 }
 
@@ -467,8 +477,7 @@ void im2col7(hipStream_t s, int N, int H, int W, int Ho, int Wo, int KP, const v
     return;
   }
   if (KP < 147 || KP % 8) fail(CKPT_E_INVALID, "im2col7: rows of 147, or of a multiple of 8 above it");
-  const int g = ew_grid(int64_t(N) * Ho * Wo * (KP / 8));
-  hipLaunchKernelGGL(k_im2col7p, dim3(g), dim3(256), 0, s, N, H, W, Ho, Wo, KP, static_cast<const __bf16 *>(X),
+  hipLaunchKernelGGL(k_im2col7p, dim3(N * Ho, (Wo + IC_WO - 1) / IC_WO), dim3(256), 0, s, N, H, W, Ho, Wo, KP, static_cast<const __bf16 *>(X),
                      static_cast<__bf16 *>(col));
 }
 

@@ -1025,7 +1025,33 @@ __global__ __launch_bounds__(64) void k_sum_partials_vec(const float4 *__restric
   out[i] = t;
 }
 
+// The first `cols` columns of `pitch`-wide rows: out[r * cols + c] = sum over b
+// of part[b][r * pitch + c].  64 slices of b per element, as k_sum_partials<64>.
+__global__ __launch_bounds__(256) void k_sum_partials_cols(const float *__restrict__ part, int nb, int rows,
+                                                           int cols, int pitch, float *__restrict__ out) {
+  __shared__ float red[64][4];
+  const int ex = threadIdx.x % 4, sl = threadIdx.x / 4;
+  const int e = blockIdx.x * 4 + ex;
+  float s = 0.f;
+  if (e < rows * cols) {
+    const float *p = part + e / cols * pitch + e % cols;
+    for (int b = sl; b < nb; b += 64) s += p[size_t(b) * rows * pitch];
+  }
+  red[sl][ex] = s;
+  __syncthreads();
+  if (sl == 0 && e < rows * cols) {
+    float t = 0.f;
+    for (int k = 0; k < 64; ++k) t += red[k][ex];
+    out[e] = t;
+  }
+}
+
 }  // namespace
+
+void sum_partials_cols(hipStream_t st, const float *part, int nb, int rows, int cols, int pitch, float *out) {
+  hipLaunchKernelGGL(k_sum_partials_cols, dim3((rows * cols + 3) / 4), dim3(256), 0, st, part, nb, rows, cols, pitch,
+                     out);
+}
 
 void sum_partials(hipStream_t st, const float *part, int nb, int E, float *out) {
   const bool vec = E % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0 &&

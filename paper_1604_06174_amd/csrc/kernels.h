@@ -238,6 +238,8 @@ void gemm_bf16_part_cat(hipStream_t s, int M, int N, int K1, const void *A1, int
                         const void *A2, int lda2, const void *B, int ldb, float *part, int splits);
 // out[e] = sum_b part[b*E + e], b in a fixed order
 void sum_partials(hipStream_t s, const float *part, int nb, int E, float *out);
+// out [rows, cols] = sum_b of the first cols columns of part[b] [rows, pitch]
+void sum_partials_cols(hipStream_t s, const float *part, int nb, int rows, int cols, int pitch, float *out);
 
 // Convolution of NHWC bf16 tensors as implicit GEMM: input [N, H, W, Ci],
 // output [N, Ho, Wo, Co], weights [Co, R, R, Ci] (bf16), stride S in {1, 2},

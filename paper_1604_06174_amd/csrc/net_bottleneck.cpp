@@ -183,6 +183,7 @@ class Bottleneck : public Net {
     ks_bnpart = take(bnpart);
     ks_sums = take(8ull * jmax);
     ks_wpart = take(wpart * 4);
+    wpart_floats = wpart;
     ks_pooled = take(4ull * N * cin);
     ks_dpool = take(4ull * N * cin);
     ks_dlog = take(4ull * N * K);
@@ -270,8 +271,7 @@ class Bottleneck : public Net {
   }
 
   // dW [M, Nn] = sum over k of A(m, k) B(k, n), A = dY^T ([Kd, M] bf16), B = X ([Kd, Nn] bf16),
-  // on stream st (with its split-K partials)
-  // (ldx: X's row pitch, Nn when 0)
+  // on stream st (with its split-K partials); ldx: X's row pitch, Nn when 0
   void wgrad_1x1(StepCtx &c, hipStream_t st, int M, int Nn, int64_t Kd, const void *dy, const void *x,
                  float *dW, int ldx = 0) {
     const int s = wsplits(M, Nn, Kd);
@@ -285,6 +285,23 @@ class Bottleneck : public Net {
       sum_partials(st, ksf(c, ks_wpart), s, M * Nn, dW);
       c.launches += 1;
     }
+  }
+
+  // the stem's weight gradient over the padded patch rows: all kStemK columns
+  // (16-byte loads, so the direct loop: 147 of them, rows of no whole number of
+  // chunks, took 239 us at batch 32, 224 x 224; 72 with the padding), in as
+  // many k splits as the partials' buffer holds, and the sums of the first 147
+  void wgrad_stem(StepCtx &c, int64_t m, const void *dy, float *dW) {
+    const int s = int(std::min<uint64_t>(uint64_t(wsplits(C0, kStemK, m)), wpart_floats / (uint64_t(C0) * kStemK)));
+    if (s < 1) return wgrad_1x1(c, c.s, C0, 147, m, dy, c.ks + ks_col, dW, kStemK);
+    GemmX gx;
+    gx.splits = s;
+    tbeg(c);
+    gemm_bf16x(c.s, C0, kStemK, int(m), dy, false, C0, false, c.ks + ks_col, kStemK, false, ksf(c, ks_wpart),
+               kStemK, GEMM_EPI_STORE, nullptr, 0, nullptr, gx);
+    tend(c, C0, 147, double(m), 2.0 * double(m) * (C0 + 147), 4.0 * C0 * 147);
+    sum_partials_cols(c.s, ksf(c, ks_wpart), s, C0, 147, kStemK, dW);
+    c.launches += 1;
   }
 
   void wgrad_conv(StepCtx &c, hipStream_t st, const ConvGeo &g, const void *x, const void *dy, float *dW) {
@@ -412,7 +429,7 @@ class Bottleneck : public Net {
       bnb_backward(c.s, m, C0, dr, r, cv, st, P(c, k.g1), bnpart(c), sums, G(c, k.g1), G(c, k.b1), dc);
       im2col7(c.s, N, S, S, side, side, kStemK, xv, c.ks + ks_col);
       c.launches += 6;
-      wgrad_1x1(c, c.s, C0, 147, m, dc, c.ks + ks_col, G(c, k.W1), kStemK);
+      wgrad_stem(c, m, dc, G(c, k.W1));
       return;
     }
     const int64_t mi = int64_t(N) * k.hin * k.hin, mo = int64_t(N) * k.hout * k.hout;
