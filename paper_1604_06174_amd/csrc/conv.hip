@@ -253,8 +253,10 @@ __global__ __launch_bounds__(256) void k_conv3x3(ConvArgs a) {
 template <int C, int J, int W, int S, int MODE, int RB, int BN>
 constexpr size_t spec_lds();
 
+// bx, by: the workgroup's row tile (of gx) and output channel block; smem holds
+// spec_lds bytes.
 template <int C, int J, int W, int S, int MODE, int EPI, int RB, int BN>
-__global__ __launch_bounds__(256) void k_conv3x3s(ConvArgs a) {
+__device__ __forceinline__ void conv3x3s_tile(const ConvArgs &a, int bx, int by, int gx, float *smem) {
   constexpr int NS = BN / 16;
   constexpr int NPIX = RB * W;
   static_assert(NPIX % 64 == 0 && C % 16 == 0 && BN % 16 == 0, "tile shape");
@@ -264,14 +266,13 @@ __global__ __launch_bounds__(256) void k_conv3x3s(ConvArgs a) {
   constexpr int HR = MODE == CONV_FWD ? (RB - 1) * S + 3 : RB + 2;
   constexpr int HC = MODE == CONV_FWD ? (W - 1) * S + 3 : W + 2;
   constexpr int WX = MODE == CONV_FWD ? W * S : W / S;  // input width
-  __shared__ __align__(16) float smem[spec_lds<C, J, W, S, MODE, RB, BN>() / 4];
   float *halo = smem;
   float *Ws = smem + HR * HC * Cs;  // all nine taps: [9][BN][Cs]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, q = lane >> 4;
   const int rblk = (a.H + RB - 1) / RB;
-  const int n = blockIdx.x / rblk, r0 = (blockIdx.x % rblk) * RB;
-  const int j0 = blockIdx.y * BN;
+  const int n = bx / rblk, r0 = (bx % rblk) * RB;
+  const int j0 = by * BN;
   const int Hx = a.Hx;
 
   // One load phase: the input halo and the weights of all nine taps are
@@ -345,7 +346,7 @@ __global__ __launch_bounds__(256) void k_conv3x3s(ConvArgs a) {
                               bn_relu(hv[k].w, tm[3], tr[3], tg[3], tb[3]));
       // stride 1: halo rows 1..RB are this workgroup's own output rows; the
       // first channel block stores them (every element once over the grid)
-      if (S == 1 && a.rout && blockIdx.y == 0) {
+      if (S == 1 && a.rout && by == 0) {
 #pragma unroll
         for (int k = 0; k < NH; ++k) {
           const int e = tid + 256 * k;
@@ -506,9 +507,15 @@ __global__ __launch_bounds__(256) void k_conv3x3s(ConvArgs a) {
       const int which = tid / BN, jj = tid % BN;
       double acc2 = 0.0;
       for (int k = 0; k < 16; ++k) acc2 += red[(k * 2 + which) * BN + jj];
-      if (j0 + jj < J) a.stats[(size_t(which) * J + j0 + jj) * gridDim.x + blockIdx.x] = acc2;
+      if (j0 + jj < J) a.stats[(size_t(which) * J + j0 + jj) * gx + bx] = acc2;
     }
   }
+}
+
+template <int C, int J, int W, int S, int MODE, int EPI, int RB, int BN>
+__global__ __launch_bounds__(256) void k_conv3x3s(ConvArgs a) {
+  __shared__ __align__(16) float smem[spec_lds<C, J, W, S, MODE, RB, BN>() / 4];
+  conv3x3s_tile<C, J, W, S, MODE, EPI, RB, BN>(a, blockIdx.x, blockIdx.y, gridDim.x, smem);
 }
 
 template <int C, int J, int W, int S, int MODE, int RB, int BN>
@@ -589,8 +596,7 @@ __device__ __forceinline__ int wg_as(int J) { return J + ((16 - J % 32) + 32) % 
 // stride (0 = take the runtime value): the network's few shapes get
 // instantiations whose index arithmetic folds to shifts and multiplies.
 template <int CT, int JT, int WT, int HT, int ST>
-__global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
-  extern __shared__ __align__(16) float smem[];
+__device__ __forceinline__ void conv3x3_wgrad_range(const WgArgs &a, int bx, int by, float *smem) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, q = lane >> 4;
   const int J = JT ? JT : a.J, C = CT ? CT : a.C, NC = 9 * C;
@@ -603,9 +609,9 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
   constexpr int BS = WG_NB;                       // == 16 mod 32
   float *Abuf = smem;                              // [2][KC][AS]
   float *Bbuf = smem + 2 * WG_KC * AS;             // [2][KC][BS]
-  const int n0 = blockIdx.y * WG_NB;
+  const int n0 = by * WG_NB;
   const int P = a.N * OH * OW;
-  const int p0 = blockIdx.x * a.pix_per_blk;
+  const int p0 = bx * a.pix_per_blk;
   const int nchunk = a.pix_per_blk / WG_KC;
 
   // staging: A = dy[p][0..16*jt_n) as float4, B = im2col[p][n0..n0+144) as float4
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
     }
   }
   if (my_kg == 0 && active) {
-    float *dst = a.part + size_t(blockIdx.x) * J * NC;
+    float *dst = a.part + size_t(bx) * J * NC;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
       const int n = n0 + t * 16 + i16;
@@ -743,6 +749,12 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
   }
 }
 
+template <int CT, int JT, int WT, int HT, int ST>
+__global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  conv3x3_wgrad_range<CT, JT, WT, HT, ST>(a, blockIdx.x, blockIdx.y, smem);
+}
+
 // ------------------------------------------- specialised weight gradient --
 // Compile-time shapes.  Workgroup = TPB tiles of RB output rows of one image
 // x one 144-column slice of n = tap*C + c (NT <= 9 tiles of 16).  The input
@@ -752,7 +764,7 @@ __global__ __launch_bounds__(256) void k_conv3x3_wgrad(WgArgs a) {
 // Wavefronts split the J row tiles and, when J < 64, the tile's pixels
 // (summed through LDS in a fixed order at the end).
 template <int C, int J, int W, int S, int RB, int TPB>
-__global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
+__device__ __forceinline__ void wgrad_s_tiles(const WgArgs &a, int bx, int by, float *smem) {
   constexpr int NC = 9 * C;
   constexpr int Cp = (C + 3) & ~3;
   constexpr int Cs = Cp + 4;
@@ -765,14 +777,13 @@ __global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
   constexpr int JS = JT * 16 + (((16 - (JT * 16) % 32) + 32) % 32);  // == 16 (mod 32)
   constexpr int NTT = (NC + 15) / 16;
   constexpr int WX = W * S;
-  extern __shared__ __align__(16) float smem[];
   float *halo = smem;
   float *dys = smem + HR * HC * Cs;  // [NPIX][JS]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, q = lane >> 4;
   const int my_jt = wave % WGJ, my_kg = wave / WGJ;
-  const int n0 = blockIdx.y * 144;
-  const int NT = min(9, NTT - blockIdx.y * 9);  // n tiles in this slice
+  const int n0 = by * 144;
+  const int NT = min(9, NTT - by * 9);  // n tiles in this slice
   const int rblk = (a.H + RB - 1) / RB;
   const int ntiles = a.N * rblk;
 
@@ -793,7 +804,7 @@ __global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
   for (int t = 0; t < 9; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   for (int tt = 0; tt < TPB; ++tt) {
-    const int g = blockIdx.x * TPB + tt;
+    const int g = bx * TPB + tt;
     if (g >= ntiles) break;
     const int img = g / rblk, r0 = (g % rblk) * RB;
     if (tt > 0) __syncthreads();
@@ -874,7 +885,7 @@ __global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
     }
   }
   if (my_kg == 0) {
-    float *dst = a.part + size_t(blockIdx.x) * J * NC;
+    float *dst = a.part + size_t(bx) * J * NC;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
       const int nn = n0 + t * 16 + i16;
@@ -886,6 +897,12 @@ __global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
       }
     }
   }
+}
+
+template <int C, int J, int W, int S, int RB, int TPB>
+__global__ __launch_bounds__(256) void k_wgrad_s(WgArgs a) {
+  extern __shared__ __align__(16) float smem[];
+  wgrad_s_tiles<C, J, W, S, RB, TPB>(a, blockIdx.x, blockIdx.y, smem);
 }
 
 template <int C, int J, int W, int S, int RB>
@@ -1119,7 +1136,7 @@ int wgrad_pix(int64_t P, int NC) {
   return int(ppb);
 }
 
-size_t wgrad_lds(int J) {
+constexpr size_t wgrad_lds(int J) {
   const int AS = (((J + 15) / 16) * 16) + ((16 - (((J + 15) / 16) * 16) % 32) + 32) % 32;
   const size_t stage = size_t(2) * WG_KC * (AS + WG_NB) * 4;
   const size_t red = size_t(4) * 9 * 4 * 64 * 4;
@@ -1150,6 +1167,48 @@ void launch_mode(const ConvArgs &a, int mode, int S, int epi, size_t lds, dim3 g
 }
 
 }  // namespace
+
+// -------------------------------------- data and weight gradient together --
+// The two gradients of a stride-1 convolution with as many inputs as outputs
+// read the same dy and nothing of each other, and neither fills the chip: at
+// batch 128 the 64-channel one is 512 + 256 workgroups of two per compute unit,
+// its 17 us of weight gradient mostly the latency of its chunk loads.  One
+// launch runs both kinds of workgroup side by side (weight gradient first: its
+// workgroups take longer); each does what its own kernel does, so the bits are
+// the same.  Batch 128, the two launches and the one: 16 channels 28.6 -> 23.7
+// us, 32 27.4 -> 23.6, 64 30.5 -> 25.5 (with the first batch norm's sums).
+// WG_RB > 0: tiles of wgrad_s; 0: pixel ranges of conv3x3_wgrad.
+template <int C, int W, int RB, int WG_RB, int WG_TPB>
+constexpr size_t pair_lds() {
+  constexpr size_t d = spec_lds<C, C, W, 1, CONV_DGRAD, RB, 16>();
+  constexpr size_t g = WG_RB ? wgs_lds<C, C, W, 1, WG_RB ? WG_RB : 1>() : wgrad_lds(C);
+  return d > g ? d : g;
+}
+
+template <int C, int W, int EPI, int RB, int WG_RB, int WG_TPB, int WPE>
+__global__ __launch_bounds__(256, WPE) void k_conv3x3_bwd(ConvArgs a, WgArgs w, int gw, int nw, int gd) {
+  __shared__ __align__(16) float smem[pair_lds<C, W, RB, WG_RB, WG_TPB>() / 4];
+  const int id = blockIdx.x;
+  if (id < nw) {
+    if constexpr (WG_RB > 0) wgrad_s_tiles<C, C, W, 1, WG_RB, WG_TPB>(w, id % gw, id / gw, smem);
+    else conv3x3_wgrad_range<C, C, W, W, 1>(w, id % gw, id / gw, smem);
+  } else {
+    conv3x3s_tile<C, C, W, 1, CONV_DGRAD, EPI, RB, 16>(a, (id - nw) % gd, (id - nw) / gd, gd, smem);
+  }
+}
+
+// Launches the pair if it is one of these shapes; *gw is then the number of
+// weight-gradient partials.  Same tiles as the separate kernels.
+template <int C, int W, int EPI, int RB, int WG_RB, int WG_TPB, int WPE>
+static bool pair_try(const ConvArgs &a, const WgArgs &w, int epi, hipStream_t st, int *gw) {
+  if (epi != EPI || a.C != C || a.J != C || a.W != W || a.H != W) return false;
+  static_assert(pair_lds<C, W, RB, WG_RB, WG_TPB>() <= 96 * 1024, "LDS");
+  const int gd = a.N * (W / RB), nd = gd * (C / 16);
+  *gw = conv3x3_wgrad_blocks(1, a.N, W, W, C, C);
+  const int nw = *gw * ((9 * C + WG_NB - 1) / WG_NB);
+  launch_timed((k_conv3x3_bwd<C, W, EPI, RB, WG_RB, WG_TPB, WPE>), dim3(nw + nd), dim3(256), 0, st, a, w, *gw, nw, gd);
+  return true;
+}
 
 static ConvArgs shape_args(int mode, int S, int N, int H, int W, int C, int J) {
   ConvArgs a{};
@@ -1244,6 +1303,21 @@ void conv3x3_wgrad(hipStream_t st, int S, const float *X, const float *DY, float
   hipLaunchKernelGGL((k_conv3x3_wgrad<0, 0, 0, 0, 0>), grid, dim3(256), lds, st, a);
 #undef CKPT_WG
   sum_partials(st, part, nbx, J * NC, dW);
+}
+
+bool conv3x3_bwd(hipStream_t st, int epi, const float *DY, const float *Wt, float *DX, const float *X, float *part,
+                 float *dW, int N, int HW, int C, const float *E0, const float *E1, double *stats, const float *tst,
+                 const float *tg, const float *tb, bool x_raw) {
+  const ConvArgs a{DY, Wt, DX, N, HW, HW, HW, HW, C, C, 0, 0, E0, E1, HW, HW, C, stats, tst, tg, tb, nullptr};
+  const WgArgs w{X,  DY, part, N, HW, HW, HW, HW, C, C, 1, wgrad_pix(int64_t(N) * HW * HW, 9 * C),
+                 x_raw ? tst : nullptr, tg, tb};
+  constexpr int MST = CONV_EPI_MASKSTATS, SC1 = CONV_EPI_SC1;
+  int gw = 0;
+  const bool ok = pair_try<16, 32, MST, 4, 4, 2, 3>(a, w, epi, st, &gw) || pair_try<16, 32, SC1, 4, 4, 2, 3>(a, w, epi, st, &gw) ||
+                  pair_try<32, 16, MST, 4, 4, 2, 4>(a, w, epi, st, &gw) || pair_try<32, 16, SC1, 4, 4, 2, 4>(a, w, epi, st, &gw) ||
+                  pair_try<64, 8, MST, 8, 0, 0, 2>(a, w, epi, st, &gw) || pair_try<64, 8, SC1, 8, 0, 0, 2>(a, w, epi, st, &gw);
+  if (ok) sum_partials(st, part, gw, 9 * C * C, dW);
+  return ok;
 }
 
 }  // namespace ckpt

@@ -94,6 +94,14 @@ bool conv3x3_supported(int mode, int S, int H, int W, int C, int J);
 void conv3x3_wgrad(hipStream_t s, int S, const float *X, const float *DY, float *part, float *dW,
                    int N, int H, int W, int Hx, int Wx, int C, int J, const float *tst = nullptr,
                    const float *tg = nullptr, const float *tb = nullptr);
+// Both gradients of a stride-1 convolution with C inputs and outputs on HW x HW
+// in one launch (and the sum of the weight-gradient partials): conv3x3(DGRAD,
+// epi MASKSTATS or SC1) into DX and conv3x3_wgrad with the input X, which is
+// bn_relu-transformed as it is read if x_raw.  False, and nothing launched, for
+// shapes without such a kernel.
+bool conv3x3_bwd(hipStream_t s, int epi, const float *DY, const float *Wt, float *DX, const float *X, float *part,
+                 float *dW, int N, int HW, int C, const float *E0, const float *E1, double *stats, const float *tst,
+                 const float *tg, const float *tb, bool x_raw);
 
 // ---- batch norm and the classifier head (bn.hip) ----
 enum { BN_RES_NONE = 0, BN_RES_ID = 1, BN_RES_A = 2 };

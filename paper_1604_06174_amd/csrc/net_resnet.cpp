@@ -202,6 +202,25 @@ class ResNetBasic : public Net {
             rout);
     timer.end(c.s, fl, by);
   }
+  // Both gradients of a stride-1 convolution with cc inputs and outputs, DX with
+  // its epilogue and the weight gradient over x: one launch where there is a
+  // kernel for the shape (counted as both convolutions' work), else two.
+  void conv_bwd(StepCtx &c, int epi, const float *DY, const float *Wt, float *DX, const float *x, float *dW, int ho,
+                int cc, const float *E0, const float *E1, const float *tst, const float *tg, const float *tb,
+                bool x_raw) {
+    const double t = 4.0 * N * ho * ho * cc, wb = 4.0 * 9.0 * cc * cc;
+    double *stats = epi == CONV_EPI_MASKSTATS ? bnpart(c) : nullptr;
+    timer.begin(c.s);
+    const bool one = conv3x3_bwd(c.s, epi, DY, Wt, DX, x, ksf(c, ks_wpart), dW, N, ho, cc, E0, E1, stats, tst, tg, tb,
+                                 x_raw);
+    // dy, the input and the epilogue's operands once, dx; weights, dW
+    timer.end(c.s, 4.0 * N * ho * ho * cc * 9.0 * cc, t * (epi == CONV_EPI_MASKSTATS ? 3 + !x_raw : 5) + 2 * wb);
+    c.launches += one ? 2 : 3;
+    if (one) return;
+    conv(c, CONV_DGRAD, 1, epi, DY, Wt, DX, ho, ho, ho, ho, cc, cc, E0, E1, E1 ? ho : 0, E1 ? ho : 0, E1 ? cc : 0, ho,
+         cc, cc, tst, tg, tb);
+    conv3x3_wgrad(c.s, 1, x, DY, ksf(c, ks_wpart), dW, N, ho, ho, ho, ho, cc, cc, x_raw ? tst : nullptr, tg, tb);
+  }
   float *ksf(StepCtx &c, uint64_t off) const { return reinterpret_cast<float *>(c.ks + off); }
 
   void fwd(int32_t i, const void *xv, void *yv, void *saved, StepCtx &c) override {
@@ -276,8 +295,6 @@ class ResNetBasic : public Net {
     // r1 as read by the second convolution's backward: stored, or c1 with its
     // batch-norm + ReLU transform
     const float *x2 = drop ? c1 : r1;
-    const float *tst = drop ? st1 : nullptr, *tg = drop ? P(c, k.g1) : nullptr,
-                *tb = drop ? P(c, k.b1) : nullptr;
     float *Pb = static_cast<float *>(qv);
     float *Qb = reinterpret_cast<float *>(static_cast<char *>(qv) + t);
     const int ho = k.hout;
@@ -287,15 +304,20 @@ class ResNetBasic : public Net {
     // statistics (the same bits as the stored relu(bn1(c1))), with the first
     // BN backward's partial sums over the masked gradient and c1 in its
     // epilogue; and conv2's weight gradient
-    conv(c, CONV_DGRAD, 1, CONV_EPI_MASKSTATS, Qb, P(c, k.w2), Pb, ho, ho, ho, ho, k.cout, k.cout, c1,
-         nullptr, 0, 0, 0, ho, k.cout, k.cout, st1, P(c, k.g1), P(c, k.b1));
-    conv3x3_wgrad(c.s, 1, x2, Qb, wpart, G(c, k.w2), N, ho, ho, ho, ho, k.cout, k.cout, tst, tg, tb);
+    conv_bwd(c, CONV_EPI_MASKSTATS, Qb, P(c, k.w2), Pb, x2, G(c, k.w2), ho, k.cout, c1, nullptr, st1, P(c, k.g1),
+             P(c, k.b1), drop);
     // first BN: finalize those sums, then its element pass
     bn_finalize_bwd(c.s, bnpart(c), conv3x3_blocks(CONV_DGRAD, 1, N, ho, ho, k.cout, k.cout), k.cout,
                     np, sums, G(c, k.g1), G(c, k.b1), true);
     bn_backward_apply(c.s, np, k.cout, Pb, nullptr, c1, st1, P(c, k.g1), sums, Qb);
-    c.launches += 8;
-    if (dxv) {  // conv1 data gradient plus the shortcut's gradient
+    c.launches += 5;
+    // conv1: data gradient plus the shortcut's gradient, weight gradient
+    if (dxv && k.stride == 1 && k.cin == k.cout) {
+      conv_bwd(c, CONV_EPI_SC1, Qb, P(c, k.w1), static_cast<float *>(dxv), x, G(c, k.w1), ho, k.cout, g, y, nullptr,
+               nullptr, nullptr, false);
+      return;
+    }
+    if (dxv) {
       conv(c, CONV_DGRAD, k.stride, k.stride == 1 ? CONV_EPI_SC1 : CONV_EPI_SC2, Qb, P(c, k.w1),
            static_cast<float *>(dxv), k.hin, k.hin, ho, ho, k.cout, k.cin, g, y, ho, ho, k.cout, ho,
            k.cin, k.cout);
