@@ -28,6 +28,7 @@
 #include "kernel_args.h"
 #include "kernels.h"
 #include "launch.h"
+#include "sum_slices.h"
 
 namespace ckpt {
 
@@ -948,14 +949,6 @@ bool wgs_dispatch(const WgArgs &a, hipStream_t st, bool launch, WgUse *u) {
 // out[e] = sum over b of part[b][e], b in a fixed order: SL slices of b
 // (slice k takes b = k, k + SL, ...), then the slices in order.  A workgroup
 // covers 256 / SL consecutive e; SL = 64 for small E, 16 otherwise.
-// Workgroups are dispatched to the eight XCDs (each with its own L2) in
-// turn; consecutive column groups are mapped to one XCD so that the cache
-// lines they share are fetched from HBM once, not once per XCD.
-__device__ __forceinline__ int xcd_grouped(int id, int G) {
-  const int q = G / 8, r = G % 8, x = id % 8, k = id / 8;
-  return x * q + (x < r ? x : r) + k;
-}
-
 template <int SL>
 __global__ __launch_bounds__(256) void k_sum_partials(const float *__restrict__ part, int nb,
                                                       int E, float *__restrict__ out) {
@@ -1307,7 +1300,7 @@ void conv3x3_wgrad(hipStream_t st, int S, const float *X, const float *DY, float
 
 bool conv3x3_bwd(hipStream_t st, int epi, const float *DY, const float *Wt, float *DX, const float *X, float *part,
                  float *dW, int N, int HW, int C, const float *E0, const float *E1, double *stats, const float *tst,
-                 const float *tg, const float *tb, bool x_raw) {
+                 const float *tg, const float *tb, bool x_raw, SumJob *sum) {
   const ConvArgs a{DY, Wt, DX, N, HW, HW, HW, HW, C, C, 0, 0, E0, E1, HW, HW, C, stats, tst, tg, tb, nullptr};
   const WgArgs w{X,  DY, part, N, HW, HW, HW, HW, C, C, 1, wgrad_pix(int64_t(N) * HW * HW, 9 * C),
                  x_raw ? tst : nullptr, tg, tb};
@@ -1316,7 +1309,7 @@ bool conv3x3_bwd(hipStream_t st, int epi, const float *DY, const float *Wt, floa
   const bool ok = pair_try<16, 32, MST, 4, 4, 2, 3>(a, w, epi, st, &gw) || pair_try<16, 32, SC1, 4, 4, 2, 3>(a, w, epi, st, &gw) ||
                   pair_try<32, 16, MST, 4, 4, 2, 4>(a, w, epi, st, &gw) || pair_try<32, 16, SC1, 4, 4, 2, 4>(a, w, epi, st, &gw) ||
                   pair_try<64, 8, MST, 8, 0, 0, 2>(a, w, epi, st, &gw) || pair_try<64, 8, SC1, 8, 0, 0, 2>(a, w, epi, st, &gw);
-  if (ok) sum_partials(st, part, gw, 9 * C * C, dW);
+  if (ok) *sum = {part, gw, 9 * C * C, dW};
   return ok;
 }
 

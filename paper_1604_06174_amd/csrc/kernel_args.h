@@ -29,6 +29,15 @@ struct WgArgs {
   const float *tst, *tg, *tb;  // optional bn_relu of the input X
 };
 
+// A sum of weight-gradient partials (sum_partials' arguments) that a later
+// launch on the same stream takes along; part and out on 16 bytes, E a multiple
+// of 4.  E == 0: none.
+struct SumJob {
+  const float *part;
+  int nb, E;
+  float *out;
+};
+
 struct GemmArgs {
   int M, N, K;
   const float *A;

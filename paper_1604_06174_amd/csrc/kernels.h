@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "kernel_args.h"
+
 namespace ckpt {
 
 // relu(gamma (x - mean) rstd + beta) with one explicit rounding sequence, so
@@ -95,13 +97,13 @@ void conv3x3_wgrad(hipStream_t s, int S, const float *X, const float *DY, float 
                    int N, int H, int W, int Hx, int Wx, int C, int J, const float *tst = nullptr,
                    const float *tg = nullptr, const float *tb = nullptr);
 // Both gradients of a stride-1 convolution with C inputs and outputs on HW x HW
-// in one launch (and the sum of the weight-gradient partials): conv3x3(DGRAD,
-// epi MASKSTATS or SC1) into DX and conv3x3_wgrad with the input X, which is
-// bn_relu-transformed as it is read if x_raw.  False, and nothing launched, for
-// shapes without such a kernel.
+// in one launch: conv3x3(DGRAD, epi MASKSTATS or SC1) into DX and the partials
+// of conv3x3_wgrad with the input X, which is bn_relu-transformed as it is read
+// if x_raw.  *sum is what is left to do for dW.  False, and nothing launched,
+// for shapes without such a kernel.
 bool conv3x3_bwd(hipStream_t s, int epi, const float *DY, const float *Wt, float *DX, const float *X, float *part,
                  float *dW, int N, int HW, int C, const float *E0, const float *E1, double *stats, const float *tst,
-                 const float *tg, const float *tb, bool x_raw);
+                 const float *tg, const float *tb, bool x_raw, SumJob *sum);
 
 // ---- batch norm and the classifier head (bn.hip) ----
 enum { BN_RES_NONE = 0, BN_RES_ID = 1, BN_RES_A = 2 };
@@ -117,7 +119,7 @@ void bn_apply(hipStream_t s, int res, int64_t P, int J, const float *Cv, const f
 // ds = Ym ? g [Ym > 0] : g; writes dgamma, dbeta and D = dL/dC.
 void bn_backward(hipStream_t s, int64_t P, int J, const float *G, const float *Ym, const float *Cv,
                  const float *st, const float *gamma, double *part, float *sums, float *dgamma,
-                 float *dbeta, float *D);
+                 float *dbeta, float *D, const SumJob &sum = {});
 // the element pass alone, D = dL/dC from the finalized sums (bn_finalize_bwd)
 void bn_backward_apply(hipStream_t s, int64_t P, int J, const float *G, const float *Ym,
                        const float *Cv, const float *st, const float *gamma, const float *sums,
@@ -150,7 +152,7 @@ void softmax_ce_rows(hipStream_t s, int N, int K, const float *L, const int *lab
 // backward partials (sum ds, sum ds xhat) of nb workgroups over m values, in
 // either layout (fp32 backward partials: channel-major; bf16: block-major)
 void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *sums,
-                     float *dgamma, float *dbeta, bool channel_major);
+                     float *dgamma, float *dbeta, bool channel_major, const SumJob &sum = {});
 
 // ---- bf16 batch norm, stem im2col and max pool (bneck.hip) ----
 enum { BNB_RES_NONE = 0, BNB_RES_ID = 1, BNB_RES_BN = 2 };

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "kernel_args.h"
 #include "launch.h"
 
 namespace ckpt {
@@ -223,6 +224,9 @@ struct StepCtx {
   // their backwards that it does for several units at once
   const std::vector<void *> *seg_saved = nullptr;
   int32_t seg_lo = 0, ready_lo = 0, ready_hi = 0;
+  // a sum of weight-gradient partials that the next launch with room for one
+  // takes along; whoever leaves one knows that a later unit's backward runs it
+  SumJob sum = {};
   // false while a forward sweep runs whose saved internals are discarded
   // (they are formed again by the unit's re-run before its backward)
   bool keep_saved = true;

@@ -27,6 +27,7 @@
 // sums again.
 // The boundary b_i is the unit's input tensor (b_0 = the image batch).
 #include <algorithm>
+#include <utility>
 
 #include "kernels.h"
 #include "net.h"
@@ -204,7 +205,10 @@ class ResNetBasic : public Net {
   }
   // Both gradients of a stride-1 convolution with cc inputs and outputs, DX with
   // its epilogue and the weight gradient over x: one launch where there is a
-  // kernel for the shape (counted as both convolutions' work), else two.
+  // kernel for the shape (counted as both convolutions' work), else two.  The
+  // first leaves the sum of its partials in c.sum for the next batch norm's
+  // backward finalize (this block's first, the block's below second, or the
+  // stem's, which is always the last), before anything writes partials again.
   void conv_bwd(StepCtx &c, int epi, const float *DY, const float *Wt, float *DX, const float *x, float *dW, int ho,
                 int cc, const float *E0, const float *E1, const float *tst, const float *tg, const float *tb,
                 bool x_raw) {
@@ -212,10 +216,10 @@ class ResNetBasic : public Net {
     double *stats = epi == CONV_EPI_MASKSTATS ? bnpart(c) : nullptr;
     timer.begin(c.s);
     const bool one = conv3x3_bwd(c.s, epi, DY, Wt, DX, x, ksf(c, ks_wpart), dW, N, ho, cc, E0, E1, stats, tst, tg, tb,
-                                 x_raw);
+                                 x_raw, &c.sum);
     // dy, the input and the epilogue's operands once, dx; weights, dW
     timer.end(c.s, 4.0 * N * ho * ho * cc * 9.0 * cc, t * (epi == CONV_EPI_MASKSTATS ? 3 + !x_raw : 5) + 2 * wb);
-    c.launches += one ? 2 : 3;
+    c.launches += one ? 1 : 3;
     if (one) return;
     conv(c, CONV_DGRAD, 1, epi, DY, Wt, DX, ho, ho, ho, ho, cc, cc, E0, E1, E1 ? ho : 0, E1 ? ho : 0, E1 ? cc : 0, ho,
          cc, cc, tst, tg, tb);
@@ -284,7 +288,8 @@ class ResNetBasic : public Net {
       const float *st = kst(c, i);
       (void)t;
       float *dc = static_cast<float *>(qv);
-      bn_backward(c.s, np, C0, g, y, cv, st, P(c, k.g1), bnpart(c), sums, G(c, k.g1), G(c, k.b1), dc);
+      bn_backward(c.s, np, C0, g, y, cv, st, P(c, k.g1), bnpart(c), sums, G(c, k.g1), G(c, k.b1), dc,
+                  std::exchange(c.sum, {}));
       conv3x3_wgrad(c.s, 1, x, dc, wpart, G(c, k.w1), N, S, S, S, S, 3, C0);
       c.launches += 5;
       return;
@@ -299,7 +304,8 @@ class ResNetBasic : public Net {
     float *Qb = reinterpret_cast<float *>(static_cast<char *>(qv) + t);
     const int ho = k.hout;
     // second BN (its input gradient is g masked by the block's final ReLU)
-    bn_backward(c.s, np, k.cout, g, y, c2, st2, P(c, k.g2), bnpart(c), sums, G(c, k.g2), G(c, k.b2), Qb);
+    bn_backward(c.s, np, k.cout, g, y, c2, st2, P(c, k.g2), bnpart(c), sums, G(c, k.g2), G(c, k.b2), Qb,
+                std::exchange(c.sum, {}));
     // conv2: data gradient masked by the first ReLU, formed from c1 and its
     // statistics (the same bits as the stored relu(bn1(c1))), with the first
     // BN backward's partial sums over the masked gradient and c1 in its
@@ -308,7 +314,7 @@ class ResNetBasic : public Net {
              P(c, k.b1), drop);
     // first BN: finalize those sums, then its element pass
     bn_finalize_bwd(c.s, bnpart(c), conv3x3_blocks(CONV_DGRAD, 1, N, ho, ho, k.cout, k.cout), k.cout,
-                    np, sums, G(c, k.g1), G(c, k.b1), true);
+                    np, sums, G(c, k.g1), G(c, k.b1), true, std::exchange(c.sum, {}));
     bn_backward_apply(c.s, np, k.cout, Pb, nullptr, c1, st1, P(c, k.g1), sums, Qb);
     c.launches += 5;
     // conv1: data gradient plus the shortcut's gradient, weight gradient

@@ -18,8 +18,10 @@ def _err(g, o):
     return float(np.max(np.abs(g - o)) / max(np.max(np.abs(o)), 1e-30))
 
 
-# (batch, seed): seeds whose ReLU decisions float32 leaves alone
-@pytest.mark.parametrize("batch,seed", [(1, 71), (3, 72), (5, 72)])
+# (batch, seed): seeds whose ReLU decisions float32 leaves alone.  Seed 72 at batch 3 is not one,
+# although the oracle's own float32 run happens to agree there: the separate launches of the two
+# gradients differ from float64 in the very bits that the joint one gives (one decision, 1.7e-2).
+@pytest.mark.parametrize("batch,seed", [(1, 71), (3, 71), (5, 72)])
 @pytest.mark.parametrize("drop", [0, 1])
 def test_gradient_pairs_against_oracle(batch, seed, drop):
     from paper_1604_06174_amd import ckpt as K
