@@ -161,7 +161,7 @@ class ResNetBasic : public Net {
     }
     grad_extra = kst;
     ks_bytes = off;
-    timed_family = "k_conv3x3< and k_conv3x3s<";
+    timed_family = "k_conv3x3<, k_conv3x3s< and k_conv3x3_bwd<";
   }
 
   double *bnpart(StepCtx &c) const { return reinterpret_cast<double *>(c.ks + ks_bnpart); }
