@@ -304,6 +304,13 @@ void head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t s
 // W_h], and the 4H H values of W_h.
 void lstm_pack_gates(hipStream_t s, int E, int H, const float *wx, const float *wh, void *dst);
 void lstm_pack_rows(hipStream_t s, int H, const float *wh, void *dst);
+// The shapes for which a direction runs so; else as a split-K product
+// (gemm_bf16_part) and a pointwise launch.
+bool lstm_step_fwd_wins(int B, int H, int E);
+bool lstm_step_bwd_wins(int B, int H);
+// z = the ns slices [B, 4H] of zpart in order + b; gates, c_out, h_out
+void lstm_fwd_point(hipStream_t s, int B, int H, const float *zpart, int ns, const float *bias,
+                    const float *c_prev, float *gates, void *h_out, float *c_out);
 // Forward: z = [x | h] [W_x; W_h] + b (x [B, E], h [B, H] bf16 or null, w
 // from lstm_pack_gates), gates [B, 4H], c_out, h_out.
 void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void *h, const void *w,
@@ -313,12 +320,18 @@ void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void
 // order + dzn [B, 4H] (bf16, may be null) times W_h^T (w from
 // lstm_pack_rows); then the gate backward.  dz must not overlap dzn.  dbp receives
 // lstm_step_row_blocks(B) records [4H] of bias-gradient column sums (one per
-// block of 16 batch rows); db_chunk adds a run of such records into db.
+// block of 16 batch rows, lstm_point_row_blocks of 4 from lstm_bwd_point);
+// db_chunk adds a run of such records into db.
 int lstm_step_row_blocks(int B);
 void lstm_step_bwd(hipStream_t s, int B, int H, const void *dzn, const void *w,
                    const float *hpart, int ns, int64_t slice, const float *dc_in, const float *gates,
                    const float *c_t, const float *c_prev, const void *h_prev, const void *h_t, void *dz,
                    float *dc_prev, void *hp_copy, void *hc_copy, float *dbp);
+// the gate backward with dh = the ns slices [B, H] of dhpart in order
+int lstm_point_row_blocks(int B);
+void lstm_bwd_point(hipStream_t s, int B, int H, const float *dhpart, int ns, const float *dc_in,
+                    const float *gates, const float *c_t, const float *c_prev, const void *h_prev,
+                    const void *h_t, void *dz, float *dc_prev, void *hp_copy, void *hc_copy, float *dbp);
 void db_chunk(hipStream_t s, int N, int nrec, const float *rec, float *db, bool first);
 void loss_reduce(hipStream_t s, int64_t rows, const float *v, float scale, float *loss);
 void fill_f32(hipStream_t s, int64_t n, float *p, float v);

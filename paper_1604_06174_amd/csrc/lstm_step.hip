@@ -1,5 +1,6 @@
 // The LSTM recurrence's two serial kernels: one time step's product and its
-// pointwise work in one launch each.
+// pointwise work in one launch each (and the pointwise work alone, for the
+// shapes that are faster with a split-K product: lstm_step_fwd_wins).
 //   forward   z = [x_t | h_{t-1}] [W_x; W_h] + b, gates, c_t, h_t
 //   backward  dh = dl_t W_o^T (slices formed ahead) + dz_{t+1} W_h^T, the gate
 //             backward: dz_t, dc_{t-1}, bias-gradient column sums
@@ -39,7 +40,37 @@ static __device__ __align__(16) const unsigned g_zero_chunks[256] = {};
 
 __device__ __forceinline__ float sigm(float x) { return 1.0f / (1.0f + expf(-x)); }
 
+// one element's gate backward: dh and the incoming dc to the gates' z gradients
+// and dc_{t-1} (none where null)
+__device__ __forceinline__ void gate_backward(float dh, float dc, float ig, float fg, float gg, float og, float c,
+                                              float c_prev, float (&dz)[4], float *dc_prev) {
+  const float tc = tanhf(c);
+  const float dct = dc + dh * og * (1.f - tc * tc);
+  dz[0] = dct * gg * ig * (1.f - ig);
+  dz[1] = dct * c_prev * fg * (1.f - fg);
+  dz[2] = dct * ig * (1.f - gg * gg);
+  dz[3] = dh * tc * og * (1.f - og);
+  if (dc_prev) *dc_prev = dct * fg;
+}
+
 typedef __attribute__((address_space(3))) void lds_void_t;
+
+// part[0] + part[slice] + ... + part[(ns - 1) slice] in that order, U loads
+// issued before any is added
+template <int U>
+__device__ __forceinline__ float slices_sum(const float *__restrict__ part, int ns, int64_t slice) {
+  float v = part[0];
+  int z = 1;
+  for (; z + U <= ns; z += U) {
+    float t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = part[(z + u) * slice];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v += t[u];
+  }
+  for (; z < ns; ++z) v += part[z * slice];
+  return v;
+}
 
 // acc[r][c] (16 x 16 tiles) += the product over the k chunks of eight
 // [g, g + G) (G / 4 MFMA steps of 32), or over [g, q1) with q1 - g < 4 (TAIL).
@@ -222,9 +253,37 @@ __global__ __launch_bounds__(64 * NW) void k_lstm_step_fwd(int B, int H, int K1,
   }
 }
 
+// The pointwise part of the forward after a split-K product, one thread per (b,
+// j): z = the ns partial slices [B, 4H] in order + bias.
+__global__ __launch_bounds__(256) void k_lstm_fwd_point(int B, int H, const float *__restrict__ zpart, int ns,
+                                                        const float *__restrict__ bias,
+                                                        const float *__restrict__ c_prev,
+                                                        float *__restrict__ gates, __bf16 *__restrict__ h_out,
+                                                        float *__restrict__ c_out) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= B * H) return;
+  const int b = e / H, j = e % H;
+  const size_t r = size_t(b) * 4 * H + j;
+  float z[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) z[g] = slices_sum<4>(zpart + r + size_t(g) * H, ns, int64_t(B) * 4 * H);
+  const float ig = sigm(z[0] + bias[j]);
+  const float fg = sigm(z[1] + bias[H + j]);
+  const float gg = tanhf(z[2] + bias[2 * H + j]);
+  const float og = sigm(z[3] + bias[3 * H + j]);
+  const float cp = c_prev ? c_prev[e] : 0.f;
+  const float c = fg * cp + ig * gg;
+  gates[r] = ig;
+  gates[r + H] = fg;
+  gates[r + 2 * size_t(H)] = gg;
+  gates[r + 3 * size_t(H)] = og;
+  c_out[e] = c;
+  h_out[e] = (__bf16)(og * tanhf(c));
+}
+
 // Backward step: tile of 16 rows x 16 hidden units.  dh = sum over z < ns of
 // hpart[z][b][j] (slices `slice` floats apart) + the product of dzn [B, 4H]
-// (null: none) and the packed W_h (see k_pack_rows) over k = 4H.  Records of 16 rows' bias-gradient
+// (null, at the last step: none) and the packed W_h (see k_pack_rows) over k = 4H.  Records of 16 rows' bias-gradient
 // column sums go to dbp[row block][4H], rows added in order.
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void k_lstm_step_bwd(
@@ -257,8 +316,7 @@ __global__ __launch_bounds__(64 * NW) void k_lstm_step_bwd(
     if (c_prev) cp = c_prev[e];
     if (h_prev) hp = h_prev[e];
     ht = h_t[e];
-    hd = hpart[e];
-    for (int s = 1; s < ns; ++s) hd += hpart[s * slice + e];
+    hd = slices_sum<8>(hpart + e, ns, slice);
   }
   if (dzn) {
     const int nq = H / 2, per = (nq + 4 * NW - 1) / (4 * NW) * 4;  // chunks of eight of 4H
@@ -278,17 +336,10 @@ __global__ __launch_bounds__(64 * NW) void k_lstm_step_bwd(
     float zv[4] = {0.f, 0.f, 0.f, 0.f};
     if (point) {
       const float dhv = dzn ? hd + sum[threadIdx.x] : hd;
-      const float ig = gv[0], fg = gv[1], gg = gv[2], og = gv[3];
-      const float tc2 = tanhf(ct);
-      const float dct = dci + dhv * og * (1.f - tc2 * tc2);
-      zv[0] = dct * gg * ig * (1.f - ig);
-      zv[1] = dct * cp * fg * (1.f - fg);
-      zv[2] = dct * ig * (1.f - gg * gg);
-      zv[3] = dhv * tc2 * og * (1.f - og);
+      gate_backward(dhv, dci, gv[0], gv[1], gv[2], gv[3], ct, cp, zv, dc_prev ? dc_prev + e : nullptr);
       __bf16 *dr = dz + size_t(b) * 4 * H + j;
 #pragma unroll
       for (int k = 0; k < 4; ++k) dr[k * H] = (__bf16)zv[k];
-      if (dc_prev) dc_prev[e] = dct * fg;
       hp_copy[e] = hp;
       hc_copy[e] = ht;
     }
@@ -305,6 +356,42 @@ __global__ __launch_bounds__(64 * NW) void k_lstm_step_bwd(
 #pragma unroll
     for (int r = 1; r < 16; ++r) v += t[r];
     dbp[size_t(tr) * 4 * H + size_t(k) * H + j0 + i16] = v;
+  }
+}
+
+// The gate backward after a split-K product, one thread per (b, j): workgroup =
+// 64 hidden units x 4 batch rows (blockIdx.y = row block).  dh = the ns partial
+// slices [B, H] in order.  The workgroup's bias-gradient column sums over its 4
+// rows, ((r0 + r1) + r2) + r3, go to dbp[blockIdx.y][4H].
+__global__ __launch_bounds__(256) void k_lstm_bwd_point(
+    int B, int H, const float *__restrict__ dhpart, int ns, const float *__restrict__ dc_in,
+    const float *__restrict__ gates, const float *__restrict__ c_t, const float *__restrict__ c_prev,
+    const __bf16 *__restrict__ h_prev, const __bf16 *__restrict__ h_t, __bf16 *__restrict__ dz,
+    float *__restrict__ dc_prev, __bf16 *__restrict__ hp_copy, __bf16 *__restrict__ hc_copy,
+    float *__restrict__ dbp) {
+  __shared__ float part[4][4][64];
+  const int cx = threadIdx.x & 63, rg = threadIdx.x >> 6;
+  const int j = blockIdx.x * 64 + cx, b = blockIdx.y * 4 + rg;
+  float zv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (j < H && b < B) {
+    const size_t e = size_t(b) * H + j;
+    const float dhv = slices_sum<8>(dhpart + e, ns, int64_t(B) * H);
+    const float *gr = gates + size_t(b) * 4 * H;
+    const float ig = gr[j], fg = gr[H + j], gg = gr[2 * H + j], og = gr[3 * H + j];
+    gate_backward(dhv, dc_in[e], ig, fg, gg, og, c_t[e], c_prev ? c_prev[e] : 0.f, zv, dc_prev ? dc_prev + e : nullptr);
+    __bf16 *dr = dz + size_t(b) * 4 * H;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dr[k * H + j] = (__bf16)zv[k];
+    hp_copy[e] = h_prev ? h_prev[e] : (__bf16)0.f;
+    hc_copy[e] = h_t[e];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) part[k][rg][cx] = zv[k];
+  __syncthreads();
+  if (j < H) {
+    const int k = rg;  // row group rg writes gate k's column sum
+    const float t = ((part[k][0][cx] + part[k][1][cx]) + part[k][2][cx]) + part[k][3][cx];
+    dbp[size_t(blockIdx.y) * 4 * H + size_t(k) * H + j] = t;
   }
 }
 
@@ -401,6 +488,42 @@ __global__ __launch_bounds__(256) void k_pack_rows(int H, const float *__restric
 
 }  // namespace
 
+// The step kernels' time is that of the rounds of one workgroup per compute unit
+// (sixteen wavefronts, 128 KB of LDS) that their tiles make, each round the
+// operand loads of its tiles; a split-K product shares loads over larger tiles
+// and needs a second launch.  Per step of T = 16, batch x hidden (input as
+// hidden), product with pointwise launch and step kernel, us:
+//   forward  1 round 64 x 1024 12.9 / 7.9; 2: 128 x 1024 15.5 / 13.2, 64 x 2048
+//            22.1 / 20.7, 32 x 4096 52.6 / 49.0; 3: 192 x 1024 18.2 / 17.9; 4:
+//            256 x 1024 20.1 / 22.6, 128 x 2048 29.9 / 34.9, 64 x 4096 59 / 72; 8:
+//            512 x 1024 29 / 44, 1024 x 512 24.5 / 30.5
+//   backward (with the head gradient, vocabulary 10,000 or 1000) 1 round 64 x 1024
+//            18.1 / 13.8, 32 x 2048 29.0 / 19.9, 16 x 4096 38.5 / 34.2; 2: 128 x
+//            1024 27.9 / 23.8, 512 x 256 20.6 / 18.5, but 64 x 2048 under the
+//            recursive plan (single steps) 34 / 41, 32 x 4096 41.1 / 43.4; 3: 256 x
+//            520 21.7 / 23.2; 4: 256 x 1024 35.7 / 42.0, 512 x 512 25.4 / 28.8,
+//            1024 x 256 27.2 / 29.9
+// With four wavefronts (k of at most 512) several workgroups share a compute
+// unit and the step kernels stay ahead: 2048 x 256 forward 22.9 / 17.2, 4096 x 128
+// 21.5 / 14.8, backward 54.7 / 46.0.
+static int rounds(int64_t workgroups) { return int((workgroups + 255) / 256); }
+
+bool lstm_step_fwd_wins(int B, int H, int E) {
+  const int rows = B <= 16 ? 16 : 32;
+  return E + H <= 512 || rounds(int64_t((B + rows - 1) / rows) * (H / 8)) <= 3;
+}
+
+bool lstm_step_bwd_wins(int B, int H) {
+  const int r = rounds(int64_t(lstm_step_row_blocks(B)) * ((H + 15) / 16));
+  return 4 * H <= 512 || r == 1 || (r == 2 && H <= 1024);
+}
+
+void lstm_fwd_point(hipStream_t s, int B, int H, const float *zpart, int ns, const float *bias,
+                    const float *c_prev, float *gates, void *h_out, float *c_out) {
+  hipLaunchKernelGGL(k_lstm_fwd_point, dim3((B * H + 255) / 256), dim3(256), 0, s, B, H, zpart, ns, bias, c_prev,
+                     gates, static_cast<__bf16 *>(h_out), c_out);
+}
+
 void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void *h, const void *w,
                    const float *bias, const float *c_prev, float *gates, void *h_out,
                    float *c_out) {
@@ -425,6 +548,16 @@ void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void
 }
 
 int lstm_step_row_blocks(int B) { return (B + 15) / 16; }
+int lstm_point_row_blocks(int B) { return (B + 3) / 4; }
+
+void lstm_bwd_point(hipStream_t s, int B, int H, const float *dhpart, int ns, const float *dc_in,
+                    const float *gates, const float *c_t, const float *c_prev, const void *h_prev,
+                    const void *h_t, void *dz, float *dc_prev, void *hp_copy, void *hc_copy, float *dbp) {
+  hipLaunchKernelGGL(k_lstm_bwd_point, dim3((H + 63) / 64, lstm_point_row_blocks(B)), dim3(256), 0, s, B, H, dhpart,
+                     ns, dc_in, gates, c_t, c_prev, static_cast<const __bf16 *>(h_prev),
+                     static_cast<const __bf16 *>(h_t), static_cast<__bf16 *>(dz), dc_prev,
+                     static_cast<__bf16 *>(hp_copy), static_cast<__bf16 *>(hc_copy), dbp);
+}
 
 void lstm_step_bwd(hipStream_t s, int B, int H, const void *dzn, const void *w,
                    const float *hpart, int ns, int64_t slice, const float *dc_in, const float *gates,

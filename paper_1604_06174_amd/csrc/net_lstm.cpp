@@ -22,13 +22,17 @@
 // the step's saved softmax-gradient buffer, then one batched softmax pass in
 // place), and the loss rows are reduced after the last backward.
 //
+// A step runs in the kernels of lstm_step.hip, one launch per direction, while
+// their tiles fill the chip few enough times; from there on in split-K products
+// with a pointwise launch, as the other GEMMs.  The choice is the shape's, not
+// the plan's.
+//
 // Static layout: boundary b = h (bf16 [B,H]) | c (fp32 [B,H]); saved a = gates
 // (fp32 [B,4H]) | softmax gradient (fp32 [B,V]); scratch q = total dh (fp32
 // [B,H]); gradient slot = dh | dc (fp32; only dc is written: the previous
-// step's backward forms dz_t W_h^T itself, in one product with its own head
-// gradient); extra gradient buffers = the chunk's
-// dz (bf16 [C*B,4H]), head gradient (bf16 [C*B,V]), h_{t-1} and h_t copies
-// (bf16 [C*B,H]).
+// step's backward forms dz_t W_h^T itself); extra gradient buffers = the
+// chunk's dz (bf16 [C*B,4H]), head gradient (bf16 [C*B,V]), h_{t-1} and h_t
+// copies (bf16 [C*B,H]).
 #include <algorithm>
 
 #include "kernels.h"
@@ -46,13 +50,18 @@ class LstmNet : public Net {
   uint64_t ga, da;  // saved parts: gates, dlog
   // operator workspace offsets
   uint64_t k_wcat, k_wot, k_wob, k_dbp, k_lossrows, k_loss, k_buf;
-  // floats of k_buf: during a segment's heads the logits' row statistics,
-  // during its backwards the head slices and, at its end, the column sums of
+  // floats of k_buf: during a step's forward the slices of z (where it is a
+  // split-K product), during a segment's heads the logits' row statistics,
+  // during its backwards the slices of dh and, at its end, the column sums of
   // the softmax gradients of the steps they were formed for
   uint64_t buf_floats;
-  int s_head;  // k slices of dl_t W_o^T
-  int nb;      // steps per batched head gradient
-  int s_one;   // k slices of [dl_t | dz_{t+1}] [W_o; W_h], chunks of one step
+  bool step_fwd;   // forward steps in one launch
+  int s_x, s_h;    // else: k slices of x W_x and h W_h
+  bool zcat;       // both as one product of [x | h] (the same slices)
+  bool step_bwd;   // backward steps form dz_{t+1} W_h^T themselves, after ...
+  int s_head;      // ... the k slices of dl_t W_o^T, else of the last step's
+  int s_one;       // else: k slices of [dl_t | dz_{t+1}] [W_o; W_h]
+  int nb;          // steps per batched head gradient
   // extra gradient buffer offsets
   uint64_t x_dz, x_dl, x_hp, x_hc;
 
@@ -90,31 +99,52 @@ class LstmNet : public Net {
     x_hc = take(uint64_t(C) * B * H * 2);
     grad_extra = off;
     off = 0;
-    k_wcat = take(uint64_t(E + H) * 4 * H * 2);  // [W_x; W_h] packed
+    step_fwd = lstm_step_fwd_wins(B, H, E);
+    // a chunk of one step has one row of dz, which the step would overwrite
+    // while its other workgroups still read it
+    step_bwd = C > 1 && lstm_step_bwd_wins(B, H);
+    k_wcat = take(uint64_t(E + H) * 4 * H * 2);  // step_fwd: [W_x; W_h] packed, else [4H][E + H]: W_x^T | W_h^T
     k_wot = take(uint64_t(H) * V * 2);
-    // [H][V] W_o and the packed W_h; chunks of one step: [H][V + 4H], W_o | W_h
+    // step_bwd: [H][V] W_o and the packed W_h, else [H][V + 4H]: W_o | W_h
     k_wob = take(uint64_t(H) * (V + 4 * H) * 2);
     // bias-gradient column sums of one chunk: per step, one [4H] record per
-    // row block of the step kernel
-    k_dbp = take(uint64_t(C) * lstm_step_row_blocks(B) * 4 * H * 4);
+    // row block of the kernel that forms them
+    k_dbp = take(uint64_t(C) * row_blocks() * 4 * H * 4);
     k_lossrows = take(uint64_t(T) * B * 4);
     k_loss = take(4);
+    // z's slices are read back by the pointwise launch right away, so it takes
+    // fewer, longer splits (about 128 workgroups per part)
+    s_x = gemm_bf16_splits(B, 4 * H, E, 128);
+    s_h = gemm_bf16_splits(B, 4 * H, H, 128);
+    zcat = E == H && s_x == s_h && gemm_bf16_kper(E, s_x) * s_x == E &&
+           gemm_bf16_kper(E + H, s_x + s_h) == gemm_bf16_kper(E, s_x);
     // head slices: four (or fewer where V is short), which give a batch of
     // seven steps 448 workgroups at the 1024/10000/64 shape and a single
     // step's product (recursive plans) 128; as many steps at once as the row
     // statistics' buffer and eight [B, H] tensors (or one of logits) hold
-    s_head = std::min(4, gemm_bf16_splits(B, H, V));
-    s_one = C == 1 ? gemm_bf16_splits(B, H, V + 4 * H) : 0;
+    s_head = gemm_bf16_splits(B, H, V);
+    s_one = gemm_bf16_splits(B, H, V + 4 * H);
     const uint64_t BH = uint64_t(B) * H, BV = uint64_t(B) * V;
-    buf_floats = std::max(std::max(BV, 8 * BH) + uint64_t(HG) * B * gemm_bf16_col_blocks(B, V) * 2,
-                          s_one * BH + V);
-    nb = int(std::min<uint64_t>(std::min(C, HG), buf_floats / (s_head * BH + V)));
+    buf_floats = std::max(BV, 8 * BH) + uint64_t(HG) * B * gemm_bf16_col_blocks(B, V) * 2;
+    if (!step_fwd) buf_floats = std::max(buf_floats, uint64_t(s_x + s_h) * 4 * BH);
+    uint64_t batched, fixed;  // floats per step of a batch, and beside them
+    if (step_bwd) {
+      s_head = std::min(4, s_head);
+      batched = s_head * BH + V;
+      fixed = 0;
+    } else {
+      batched = V;
+      fixed = uint64_t(std::max(s_head, s_one)) * BH;
+    }
+    buf_floats = std::max(buf_floats, fixed + batched);
+    nb = int(std::min<uint64_t>(std::min(C, HG), (buf_floats - fixed) / batched));
     k_buf = take(buf_floats * 4);
     ks_bytes = off;
     timed_family = "k_gemm_bf16";
   }
 
-  int ld_wo() const { return C > 1 ? V : V + 4 * H; }
+  int row_blocks() const { return step_bwd ? lstm_step_row_blocks(B) : lstm_point_row_blocks(B); }
+  int ld_wo() const { return step_bwd ? V : V + 4 * H; }
   char *K(StepCtx &c, uint64_t o) const { return c.ks + o; }
   float *Kf(StepCtx &c, uint64_t o) const { return reinterpret_cast<float *>(c.ks + o); }
   char *X(StepCtx &c, uint64_t o) const { return c.gextra + o; }
@@ -129,14 +159,14 @@ class LstmNet : public Net {
               2.0 * (double(M) * Kd + double(Kd) * N) + (epi == GEMM_EPI_ADD ? 8.0 : 4.0) * M * N);
     c.launches += 1;
   }
-  // split-K partial products into the slices of k_buf.
+  // split-K partial products into slices [z0, z0 + splits) of k_buf.
   // Algorithmic bytes: each operand read once and the product written once
   // (the slices are this implementation's, not the product's, traffic).
   void gemm_part(StepCtx &c, int M, int N, int Kd, const void *A, int lda, const void *Bm, int ldb,
-                 int splits) {
+                 int z0, int splits) {
     timer.begin(c.s);
     gemm_bf16_part(c.s, M, N, Kd, A, false, lda, true, Bm, ldb, true,
-                   Kf(c, k_buf), splits);
+                   Kf(c, k_buf) + size_t(z0) * M * N, splits);
     timer.end(c.s, 2.0 * M * N * Kd, 2.0 * (double(M) * Kd + double(Kd) * N) + 4.0 * M * N);
     c.launches += 1;
   }
@@ -144,10 +174,15 @@ class LstmNet : public Net {
   void begin_step(StepCtx &c) override {
     // bf16 copies of the weights: in the step kernels' operand order, and
     // k contiguous for the GEMMs
-    lstm_pack_gates(c.s, E, H, P(c, pWx), P(c, pWh), K(c, k_wcat));
+    if (step_fwd) {
+      lstm_pack_gates(c.s, E, H, P(c, pWx), P(c, pWh), K(c, k_wcat));
+    } else {
+      transpose_bf16(c.s, E, 4 * H, P(c, pWx), K(c, k_wcat), E + H);                  // [4H][0, E)
+      transpose_bf16(c.s, H, 4 * H, P(c, pWh), K(c, k_wcat) + size_t(E) * 2, E + H);  // [4H][E, E + H)
+    }
     transpose_bf16(c.s, H, V, P(c, pWo), K(c, k_wot));        // [V][H]
     cvt_bf16_rows(c.s, H, V, P(c, pWo), K(c, k_wob), ld_wo());                    // [H][0, V)
-    if (C > 1)
+    if (step_bwd)
       lstm_pack_rows(c.s, H, P(c, pWh), K(c, k_wob) + size_t(H) * V * 2);
     else
       cvt_bf16_rows(c.s, H, 4 * H, P(c, pWh), K(c, k_wob) + size_t(V) * 2, ld_wo());  // [H][V, V + 4H)
@@ -159,9 +194,26 @@ class LstmNet : public Net {
     char *y = static_cast<char *>(yv);
     char *sv = static_cast<char *>(saved);
     const void *xt = static_cast<const char *>(c.input) + size_t(i) * B * E * 2;
-    lstm_step_fwd(c.s, B, H, E, xt, i > 0 ? x : nullptr, K(c, k_wcat), P(c, pb),
-                  i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr, reinterpret_cast<float *>(sv), y,
-                  reinterpret_cast<float *>(y + hb));
+    const float *c_prev = i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr;
+    float *gates = reinterpret_cast<float *>(sv), *c_out = reinterpret_cast<float *>(y + hb);
+    if (step_fwd) {
+      lstm_step_fwd(c.s, B, H, E, xt, i > 0 ? x : nullptr, K(c, k_wcat), P(c, pb), c_prev, gates, y, c_out);
+      c.launches += 1;
+      return;
+    }
+    // both products split over k into one slice buffer that the pointwise
+    // kernel adds up in order with the bias
+    if (i > 0 && zcat) {
+      timer.begin(c.s);
+      gemm_bf16_part_cat(c.s, B, 4 * H, E, xt, E, H, x, H, K(c, k_wcat), E + H, Kf(c, k_buf), s_x + s_h);
+      timer.end(c.s, 2.0 * B * 4 * H * (E + H),
+                2.0 * (double(B) * (E + H) + double(E + H) * 4 * H) + 4.0 * B * 4 * H);
+      c.launches += 1;
+    } else {
+      gemm_part(c, B, 4 * H, E, xt, E, K(c, k_wcat), E + H, 0, s_x);
+      if (i > 0) gemm_part(c, B, 4 * H, H, x, H, K(c, k_wcat) + size_t(E) * 2, E + H, s_x, s_h);
+    }
+    lstm_fwd_point(c.s, B, H, Kf(c, k_buf), s_x + (i > 0 ? s_h : 0), P(c, pb), c_prev, gates, y, c_out);
     c.launches += 1;
     // the step's head runs after the kept forward of its segment (fwd_segment)
   }
@@ -225,7 +277,7 @@ class LstmNet : public Net {
               X(c, x_dl) + size_t(i - t0) * B * V * 2, Kf(c, k_buf) + buf_floats - uint64_t(nb) * V,
               G(c, pbo), i == n - 1);
     c.launches += 2;
-    if (C > 1) gemm_part(c, nu * B, H, V, dl, V, K(c, k_wob), ld_wo(), s_head);
+    if (step_bwd) gemm_part(c, nu * B, H, V, dl, V, K(c, k_wob), ld_wo(), 0, s_head);
     c.ready_lo = lo;
     c.ready_hi = i + 1;
   }
@@ -241,7 +293,7 @@ class LstmNet : public Net {
     const int t0 = (i / C) * C;
     const size_t row = size_t(i - t0) * B;
     const bool last = i == n - 1;
-    const int t_end = std::min(t0 + C, int(n)), rb = lstm_step_row_blocks(B);
+    const int t_end = std::min(t0 + C, int(n)), rb = row_blocks();
     char *dz = X(c, x_dz) + row * 4 * H * 2;
     (void)qv;
     if (i < c.ready_lo || i >= c.ready_hi) head_grads(i, sv, c);
@@ -251,30 +303,31 @@ class LstmNet : public Net {
     // chunk is a single step, where both parts are formed by one product
     // before the gate backward overwrites it)
     const char *dzn = last ? nullptr : X(c, x_dz) + size_t((i + 1) % C) * B * 4 * H * 2;
-    const float *hp = Kf(c, k_buf) + size_t(i - c.ready_lo) * B * H;
-    int ns = s_head;
-    int64_t slice = int64_t(c.ready_hi - c.ready_lo) * B * H;
-    if (C == 1) {
-      const char *dl = X(c, x_dl);
-      slice = int64_t(B) * H;
+    const float *gates = reinterpret_cast<const float *>(sv), *c_t = reinterpret_cast<const float *>(y + hb),
+                *dc_in = reinterpret_cast<const float *>(g + gh),
+                *c_prev = i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr;
+    const char *h_prev = i > 0 ? x : nullptr;
+    float *dc_prev = dx ? reinterpret_cast<float *>(dx + gh) : nullptr;
+    char *hp = X(c, x_hp) + row * H * 2, *hc = X(c, x_hc) + row * H * 2;
+    float *dbp = Kf(c, k_dbp) + size_t(t_end - 1 - i) * rb * 4 * H;
+    if (step_bwd) {
+      lstm_step_bwd(c.s, B, H, dzn, K(c, k_wob) + size_t(H) * V * 2, Kf(c, k_buf) + size_t(i - c.ready_lo) * B * H,
+                    s_head, int64_t(c.ready_hi - c.ready_lo) * B * H, dc_in, gates, c_t, c_prev, h_prev, y, dz, dc_prev,
+                    hp, hc, dbp);
+    } else {
+      const char *dl = X(c, x_dl) + row * V * 2;
       if (last) {
-        gemm_part(c, B, H, V, dl, V, K(c, k_wob), ld_wo(), s_head);
+        gemm_part(c, B, H, V, dl, V, K(c, k_wob), ld_wo(), 0, s_head);
       } else {
         timer.begin(c.s);
         gemm_bf16_part_cat(c.s, B, H, V, dl, V, 4 * H, dzn, 4 * H, K(c, k_wob), ld_wo(), Kf(c, k_buf), s_one);
         timer.end(c.s, 2.0 * B * H * (V + 4.0 * H),
                   2.0 * (double(B) * (V + 4 * H) + double(V + 4 * H) * H) + 4.0 * B * H);
         c.launches += 1;
-        ns = s_one;
-        dzn = nullptr;
       }
+      lstm_bwd_point(c.s, B, H, Kf(c, k_buf), last ? s_head : s_one, dc_in, gates, c_t, c_prev, h_prev, y, dz,
+                     dc_prev, hp, hc, dbp);
     }
-    lstm_step_bwd(c.s, B, H, dzn, K(c, k_wob) + size_t(H) * V * 2, hp, ns, slice,
-                  reinterpret_cast<const float *>(g + gh), reinterpret_cast<const float *>(sv),
-                  reinterpret_cast<const float *>(y + hb),
-                  i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr, i > 0 ? x : nullptr, y, dz,
-                  dx ? reinterpret_cast<float *>(dx + gh) : nullptr, X(c, x_hp) + row * H * 2,
-                  X(c, x_hc) + row * H * 2, Kf(c, k_dbp) + size_t(t_end - 1 - i) * rb * 4 * H);
     c.launches += 1;
     if (i == t0) {  // the chunk [t0, t0 + C) is complete: its weight gradients
       const int rows = (t_end - t0) * B;

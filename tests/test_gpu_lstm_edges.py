@@ -3,8 +3,10 @@ and bit-identity checks of test_gpu_lstm on shapes with one row, one row past a
 16- and a 32-row tile, hidden sizes that leave a partial 16-column tile, k
 ranges on both sides of the four / sixteen wavefront rule with fewer k steps
 than wavefronts, an input of another size than the state, chunks of one step
-(where the recurrent product takes its own launch) and chunks that no batch of
-head gradients divides."""
+(where the recurrent product takes its own launch), chunks that no batch of
+head gradients divides, and batches on the far side of the step kernels' rules:
+both directions as products with the input and state parts of z apart and as
+one, and only the backward so."""
 import pytest
 
 import test_gpu_lstm as base
@@ -17,6 +19,9 @@ EDGES = {
     "rows33_k520": dict(T=6, batch=33, input=456, hidden=64, vocab=136, grad_chunk=0),
     "hidden136": dict(T=11, batch=16, input=16, hidden=136, vocab=304, grad_chunk=10),
     "chunk1": dict(T=6, batch=5, input=24, hidden=40, vocab=56, grad_chunk=1),
+    "products": dict(T=4, batch=800, input=256, hidden=264, vocab=72, grad_chunk=3),
+    "products_cat": dict(T=4, batch=640, input=320, hidden=320, vocab=40, grad_chunk=3),
+    "product_backward": dict(T=4, batch=288, input=24, hidden=520, vocab=40, grad_chunk=3),
 }
 
 
