@@ -296,9 +296,9 @@ void softmax_ce_tiles_batched(hipStream_t s, int nunits, int rows, int V, float 
                               float *loss_rows);
 // Steps' softmax gradients for the backward, step u = 0 .. nu-1 at dlog - u sd
 // (fp32 [B, V]): their bf16 copies at dl - u B V, their column sums to cs
-// [nu][V], and db (+)= those, in order of u.
-void head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t sd, void *dl, float *cs,
-               float *db, bool first);
+// [nu][V], and db (+)= those, in order of u.  Returns the launches.
+int head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t sd, void *dl, float *cs,
+              float *db, bool first);
 // ---- one LSTM step per launch (lstm_step.hip) ----
 // The weights in the steps' operand order (bf16): (E + H) 4H values of [W_x;
 // W_h], and the 4H H values of W_h.

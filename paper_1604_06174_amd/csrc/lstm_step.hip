@@ -399,9 +399,11 @@ __global__ __launch_bounds__(256) void k_lstm_bwd_point(
 // 1, ...) with their bf16 copies: step u's gradient at dlog - u sd, its copy
 // at dl - u B V.  Workgroup = 32 columns x 16 row groups of one step; group rg
 // takes rows rg, rg + 16, ..., issuing four row loads before it uses any, and
-// the groups combine as a fixed pairwise tree.  cs[u][v] = the step's sum.
+// the groups combine as a fixed pairwise tree.  cs[u][v] = the step's sum, which
+// a launch of a single step adds to db itself (when given).
 __global__ __launch_bounds__(512) void k_head_prep(int B, int V, const float *__restrict__ dlog, int64_t sd,
-                                                   __bf16 *__restrict__ dl, float *__restrict__ cs) {
+                                                   __bf16 *__restrict__ dl, float *__restrict__ cs,
+                                                   float *__restrict__ db, int first) {
   __shared__ float part[16][32];
   const int cx = threadIdx.x & 31, rg = threadIdx.x >> 5;
   const int v = blockIdx.x * 32 + cx;
@@ -432,7 +434,9 @@ __global__ __launch_bounds__(512) void k_head_prep(int B, int V, const float *__
     float q[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) q[i] = part[2 * i][cx] + part[2 * i + 1][cx];
-    cs[u * V + v] = (((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
+    const float t = (((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
+    if (db) db[v] = first ? t : db[v] + t;
+    else cs[u * V + v] = t;
   }
 }
 
@@ -589,11 +593,13 @@ void lstm_pack_rows(hipStream_t s, int H, const float *wh, void *dst) {
                      static_cast<__bf16 *>(dst));
 }
 
-void head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t sd, void *dl, float *cs,
-               float *db, bool first) {
+int head_prep(hipStream_t s, int nu, int B, int V, const float *dlog, int64_t sd, void *dl, float *cs,
+              float *db, bool first) {
   hipLaunchKernelGGL(k_head_prep, dim3((V + 31) / 32, nu), dim3(512), 0, s, B, V, dlog, sd,
-                     static_cast<__bf16 *>(dl), cs);
+                     static_cast<__bf16 *>(dl), cs, nu == 1 ? db : nullptr, first ? 1 : 0);
+  if (nu == 1) return 1;
   hipLaunchKernelGGL(k_head_db, dim3((V + 255) / 256), dim3(256), 0, s, V, nu, cs, db, first ? 1 : 0);
+  return 2;
 }
 
 }  // namespace ckpt

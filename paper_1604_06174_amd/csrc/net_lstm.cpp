@@ -273,10 +273,9 @@ class LstmNet : public Net {
     }
     const int nu = i - lo + 1;
     char *dl = X(c, x_dl) + size_t(lo - t0) * B * V * 2;
-    head_prep(c.s, nu, B, V, reinterpret_cast<const float *>(saved + ga), sd / 4,
-              X(c, x_dl) + size_t(i - t0) * B * V * 2, Kf(c, k_buf) + buf_floats - uint64_t(nb) * V,
-              G(c, pbo), i == n - 1);
-    c.launches += 2;
+    c.launches += head_prep(c.s, nu, B, V, reinterpret_cast<const float *>(saved + ga), sd / 4,
+                            X(c, x_dl) + size_t(i - t0) * B * V * 2,
+                            Kf(c, k_buf) + buf_floats - uint64_t(nb) * V, G(c, pbo), i == n - 1);
     if (step_bwd) gemm_part(c, nu * B, H, V, dl, V, K(c, k_wob), ld_wo(), 0, s_head);
     c.ready_lo = lo;
     c.ready_hi = i + 1;
