@@ -1,6 +1,6 @@
 // The LSTM recurrence's two serial kernels: one time step's product and its
 // pointwise work in one launch each (and the pointwise work alone, for the
-// shapes that are faster with a split-K product: lstm_step_fwd_wins).
+// shapes that are faster with a split-K product: lstm_step_fwd_wins, lstm_step_bwd_wins).
 //   forward   z = [x_t | h_{t-1}] [W_x; W_h] + b, gates, c_t, h_t
 //   backward  dh = dl_t W_o^T (slices formed ahead) + dz_{t+1} W_h^T, the gate
 //             backward: dz_t, dc_{t-1}, bias-gradient column sums
@@ -55,21 +55,35 @@ __device__ __forceinline__ void gate_backward(float dh, float dc, float ig, floa
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
-// part[0] + part[slice] + ... + part[(ns - 1) slice] in that order, U loads
-// issued before any is added
-template <int U>
-__device__ __forceinline__ float slices_sum(const float *__restrict__ part, int ns, int64_t slice) {
-  float v = part[0];
+// NV sums v[k] = part[k d] + part[slice + k d] + ... over the ns slices in that
+// order; U slices are loaded for all of them before any is added, so a round's
+// loads are in flight together
+template <int NV, int U>
+__device__ __forceinline__ void slices_sum(const float *__restrict__ part, int64_t d, int ns, int64_t slice,
+                                           float (&v)[NV]) {
+#pragma unroll
+  for (int k = 0; k < NV; ++k) v[k] = part[k * d];
   int z = 1;
   for (; z + U <= ns; z += U) {
-    float t[U];
+    float t[U][NV];
 #pragma unroll
-    for (int u = 0; u < U; ++u) t[u] = part[(z + u) * slice];
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-    for (int u = 0; u < U; ++u) v += t[u];
+      for (int k = 0; k < NV; ++k) t[u][k] = part[(z + u) * slice + k * d];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < NV; ++k) v[k] += t[u][k];
   }
-  for (; z < ns; ++z) v += part[z * slice];
-  return v;
+  for (; z < ns; ++z)
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] += part[z * slice + k * d];
+}
+template <int U>
+__device__ __forceinline__ float slices_sum(const float *__restrict__ part, int ns, int64_t slice) {
+  float v[1];
+  slices_sum<1, U>(part, 0, ns, slice, v);
+  return v[0];
 }
 
 // acc[r][c] (16 x 16 tiles) += the product over the k chunks of eight
@@ -265,8 +279,7 @@ __global__ __launch_bounds__(256) void k_lstm_fwd_point(int B, int H, const floa
   const int b = e / H, j = e % H;
   const size_t r = size_t(b) * 4 * H + j;
   float z[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g) z[g] = slices_sum<4>(zpart + r + size_t(g) * H, ns, int64_t(B) * 4 * H);
+  slices_sum<4, 4>(zpart + r, H, ns, int64_t(B) * 4 * H, z);
   const float ig = sigm(z[0] + bias[j]);
   const float fg = sigm(z[1] + bias[H + j]);
   const float gg = tanhf(z[2] + bias[2 * H + j]);
@@ -495,18 +508,19 @@ __global__ __launch_bounds__(256) void k_pack_rows(int H, const float *__restric
 // The step kernels' time is that of the rounds of one workgroup per compute unit
 // (sixteen wavefronts, 128 KB of LDS) that their tiles make, each round the
 // operand loads of its tiles; a split-K product shares loads over larger tiles
-// and needs a second launch.  Per step of T = 16, batch x hidden (input as
-// hidden), product with pointwise launch and step kernel, us:
-//   forward  1 round 64 x 1024 12.9 / 7.9; 2: 128 x 1024 15.5 / 13.2, 64 x 2048
-//            22.1 / 20.7, 32 x 4096 52.6 / 49.0; 3: 192 x 1024 18.2 / 17.9; 4:
-//            256 x 1024 20.1 / 22.6, 128 x 2048 29.9 / 34.9, 64 x 4096 59 / 72; 8:
-//            512 x 1024 29 / 44, 1024 x 512 24.5 / 30.5
-//   backward (with the head gradient, vocabulary 10,000 or 1000) 1 round 64 x 1024
-//            18.1 / 13.8, 32 x 2048 29.0 / 19.9, 16 x 4096 38.5 / 34.2; 2: 128 x
-//            1024 27.9 / 23.8, 512 x 256 20.6 / 18.5, but 64 x 2048 under the
-//            recursive plan (single steps) 34 / 41, 32 x 4096 41.1 / 43.4; 3: 256 x
-//            520 21.7 / 23.2; 4: 256 x 1024 35.7 / 42.0, 512 x 512 25.4 / 28.8,
-//            1024 x 256 27.2 / 29.9
+// and needs a second launch.  One round: always the step kernels.  More: while
+// the operands of all rounds are short enough.  48 steps under the sqrt /
+// recursive plan (vocabulary 10,000, and 1000 at hidden 512), us, products in
+// both directions and step kernels in those that the rules give:
+//   32 x 2048 (1 round) 3856 / 5999 and 3149 / 5522;  128 x 1024 (2) 3361 / 5090
+//   and 3171 / 5081;  256 x 512 (2) 1932 / 3573 and 1906 / 3372;  256 x 520 with
+//   an input of 136 (3 forward, the backward as a product) 2438 / 4487 and 2102 /
+//   3771
+// Past the rules, products in both directions and step kernels forward: 64 x
+// 1536 (2) 3467 / 5427 and 3556 / 5617, 64 x 2048 (2) 4398 / 6749 and 4423 /
+// 7334, 192 x 1024 (3) 4586 / 6642 and 4677 / 6759; and per backward step,
+// product and step kernel: 256 x 520 (3) 21.7 / 23.2, 512 x 512 (4) 25.4 / 28.8,
+// 1024 x 256 (4) 27.2 / 29.9, 256 x 1024 (4) 35.7 / 42.0.
 // With four wavefronts (k of at most 512) several workgroups share a compute
 // unit and the step kernels stay ahead: 2048 x 256 forward 22.9 / 17.2, 4096 x 128
 // 21.5 / 14.8, backward 54.7 / 46.0.
@@ -514,7 +528,8 @@ static int rounds(int64_t workgroups) { return int((workgroups + 255) / 256); }
 
 bool lstm_step_fwd_wins(int B, int H, int E) {
   const int rows = B <= 16 ? 16 : 32;
-  return E + H <= 512 || rounds(int64_t((B + rows - 1) / rows) * (H / 8)) <= 3;
+  const int r = rounds(int64_t((B + rows - 1) / rows) * (H / 8));
+  return E + H <= 512 || r == 1 || int64_t(r) * (E + H) <= 4096;
 }
 
 bool lstm_step_bwd_wins(int B, int H) {

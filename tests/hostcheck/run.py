@@ -374,7 +374,7 @@ def dry_runs(quick):
                   name="lstm small"),
              dict(kind="lstm", T=7, batch=17, input=40, hidden=24, vocab=72, grad_chunk=1,
                   name="lstm chunks of one step"),
-             dict(kind="lstm", T=5, batch=800, input=256, hidden=264, vocab=72, grad_chunk=3,
+             dict(kind="lstm", T=5, batch=544, input=1144, hidden=264, vocab=72, grad_chunk=3,
                   name="lstm large batch"),
              dict(kind="lstm", T=5, batch=288, input=24, hidden=520, vocab=40, grad_chunk=3,
                   name="lstm product backward"),

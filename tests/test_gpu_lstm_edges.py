@@ -19,8 +19,8 @@ EDGES = {
     "rows33_k520": dict(T=6, batch=33, input=456, hidden=64, vocab=136, grad_chunk=0),
     "hidden136": dict(T=11, batch=16, input=16, hidden=136, vocab=304, grad_chunk=10),
     "chunk1": dict(T=6, batch=5, input=24, hidden=40, vocab=56, grad_chunk=1),
-    "products": dict(T=4, batch=800, input=256, hidden=264, vocab=72, grad_chunk=3),
-    "products_cat": dict(T=4, batch=640, input=320, hidden=320, vocab=40, grad_chunk=3),
+    "products": dict(T=4, batch=544, input=1144, hidden=264, vocab=72, grad_chunk=3),
+    "products_cat": dict(T=4, batch=192, input=704, hidden=704, vocab=40, grad_chunk=3),
     "product_backward": dict(T=4, batch=288, input=24, hidden=520, vocab=40, grad_chunk=3),
 }
 
