@@ -123,22 +123,25 @@ __device__ __forceinline__ void finalize_channel(int j, int J, double sa, double
   }
 }
 
-// Channel-major partials: a workgroup per channel.
-template <bool FWD>
-__device__ __forceinline__ void finalize_cm(const double *__restrict__ part, int nb, int J, double m,
-                                            float *__restrict__ out, float *__restrict__ dgamma,
-                                            float *__restrict__ dbeta) {
+// A workgroup per channel, of channel-major (CM) or block-major partials.
+template <bool FWD, bool CM>
+__device__ __forceinline__ void finalize_one(const double *__restrict__ part, int nb, int J, double m,
+                                             float *__restrict__ out, float *__restrict__ dgamma,
+                                             float *__restrict__ dbeta) {
   __shared__ double r0[4], r1[4];
   const int j = blockIdx.x;
-  const double *p0 = part + size_t(j) * nb, *p1 = part + (size_t(J) + j) * nb;
+  // element k of sum w at p_w[k * step]
+  const double *p0 = CM ? part + size_t(j) * nb : part + j;
+  const double *p1 = CM ? part + (size_t(J) + j) * nb : part + J + j;
+  const size_t step = CM ? 1 : size_t(2) * J;
   double a = 0, b = 0;
   int k = threadIdx.x;
   for (; k + 3 * 256 < nb; k += 4 * 256) {  // four partials of each sum in flight
     double ta[4], tb[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      ta[u] = p0[k + 256 * u];
-      tb[u] = p1[k + 256 * u];
+      ta[u] = p0[(k + 256 * u) * step];
+      tb[u] = p1[(k + 256 * u) * step];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -147,8 +150,8 @@ __device__ __forceinline__ void finalize_cm(const double *__restrict__ part, int
     }
   }
   for (; k < nb; k += 256) {
-    a += p0[k];
-    b += p1[k];
+    a += p0[k * step];
+    b += p1[k * step];
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -166,12 +169,12 @@ __device__ __forceinline__ void finalize_cm(const double *__restrict__ part, int
                           out, dgamma, dbeta);
 }
 
-template <bool FWD>
+template <bool FWD, bool CM>
 __global__ __launch_bounds__(256) void k_bn_finalize(const double *__restrict__ part, int nb, int J,
                                                      double m, float *__restrict__ out,
                                                      float *__restrict__ dgamma,
                                                      float *__restrict__ dbeta) {
-  finalize_cm<FWD>(part, nb, J, m, out, dgamma, dbeta);
+  finalize_one<FWD, CM>(part, nb, J, m, out, dgamma, dbeta);
 }
 
 // The same for a backward, and beside it the sum of a convolution's
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(256) void k_bn_finalize_sum(const double *__restric
                                                          float4 *__restrict__ dw) {
   __shared__ float4 red[16 * 64];
   const int blk = int(blockIdx.x) - J;
-  if (blk < 0) finalize_cm<false>(part, nb, J, m, out, dgamma, dbeta);
+  if (blk < 0) finalize_one<false, true>(part, nb, J, m, out, dgamma, dbeta);
   else if (E4 >= SUM_SLICES16_E4) sum_slices16(wpart, nw, E4, dw, blk, red);
   else sum_slices64(wpart, nw, E4, dw, xcd_grouped(blk, int(gridDim.x) - J), red);
 }
@@ -673,13 +676,29 @@ static int64_t bn_pb(int64_t P, int J) {
   return (P + nb - 1) / nb;
 }
 
+// Long partials of few channels: eight channels per workgroup would leave them
+// to few compute units.  1568 / 3136 / 6272 rows of 64 channels after the stem's
+// convolution 8.1 / 18.6 / 35.2 us so, 6.6 / 12.7 / 22.1 with a workgroup per
+// channel; 784 and fewer 4.6 both ways.  From 65 channels on the same while the
+// rows fit one XCD's L2, which every workgroup reads them through (1568 x 128
+// 5.0 and 4.4; 2352 x 128 6.4 and 10.1).
+static bool bn_per_channel(int nb, int J) { return nb > 1024 && (J <= 64 || int64_t(nb) * J * 16 <= (4 << 20)); }
+
+template <bool FWD>
+static void bn_finalize(hipStream_t s, const double *part, int nb, int J, int64_t m, float *out, float *dgamma,
+                        float *dbeta, bool channel_major) {
+  if (channel_major)
+    hipLaunchKernelGGL((k_bn_finalize<FWD, true>), dim3(J), dim3(256), 0, s, part, nb, J, double(m), out, dgamma, dbeta);
+  else if (bn_per_channel(nb, J))
+    hipLaunchKernelGGL((k_bn_finalize<FWD, false>), dim3(J), dim3(256), 0, s, part, nb, J, double(m), out, dgamma, dbeta);
+  else
+    hipLaunchKernelGGL(k_bn_finalize_rows<FWD>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), out, dgamma,
+                       dbeta);
+}
+
 void bn_finalize_fwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *st,
                      bool channel_major) {
-  if (channel_major)
-    hipLaunchKernelGGL(k_bn_finalize<true>, dim3(J), dim3(256), 0, s, part, nb, J, double(m), st, nullptr, nullptr);
-  else
-    hipLaunchKernelGGL(k_bn_finalize_rows<true>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), st,
-                       nullptr, nullptr);
+  bn_finalize<true>(s, part, nb, J, m, st, nullptr, nullptr, channel_major);
 }
 
 void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *sums,
@@ -692,11 +711,7 @@ void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m
     return;
   }
   if (E4) sum_partials(s, sum.part, sum.nb, sum.E, sum.out);
-  if (channel_major)
-    hipLaunchKernelGGL(k_bn_finalize<false>, dim3(J), dim3(256), 0, s, part, nb, J, double(m), sums, dgamma, dbeta);
-  else
-    hipLaunchKernelGGL(k_bn_finalize_rows<false>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), sums,
-                       dgamma, dbeta);
+  bn_finalize<false>(s, part, nb, J, m, sums, dgamma, dbeta, channel_major);
 }
 
 void bn_apply(hipStream_t s, int res, int64_t P, int J, const float *Cv, const float *st,
