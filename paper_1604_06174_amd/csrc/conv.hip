@@ -1001,9 +1001,10 @@ __global__ __launch_bounds__(256) void k_sum_partials_seq(const float4 *__restri
 // k_sum_partials<16>'s sum for any nb, four consecutive e per thread: the
 // thread keeps all sixteen slices' sums itself (slice k adds part[k],
 // part[k + 16], ..., then the slices are added in order), sixteen 16-byte loads
-// in flight.  One wavefront per workgroup, so that 36,864 threads (128 x 128 x
-// 9 weights) still give 576 workgroups.  56 partials of those: 9.8 us as
-// k_sum_partials<16> (4-byte loads), 7.5 so; 24 of 1024 x 256: 10.8 and 6.0.
+// in flight, one wavefront per workgroup: for sums of so many e that one
+// wavefront per 256 of them fills the chip.  24 of 1024 x 256, 24 of 512 x 512 x 9:
+// 10.1 and 75.7 us as k_sum_partials<16> (4-byte loads), 3.9 and 34.4 so; the
+// first 4.4 as k_sum_slices16.
 __global__ __launch_bounds__(64) void k_sum_partials_vec(const float4 *__restrict__ part, int nb, int E4,
                                                          float4 *__restrict__ out) {
   const int i = blockIdx.x * 64 + threadIdx.x;
@@ -1033,6 +1034,16 @@ __global__ __launch_bounds__(64) void k_sum_partials_vec(const float4 *__restric
     t.w += s[k].w;
   }
   out[i] = t;
+}
+
+// The same sum for fewer e: the four wavefronts of a workgroup share the sixteen
+// slices of its 256 e, so four times as many loads are in flight.  56 partials of
+// 128 x 128 x 9: 9.8 us as k_sum_partials<16>, 4.6 so; 128 of 36,864: 4.6, 3.9
+// (6.0 in one wavefront).
+__global__ __launch_bounds__(256) void k_sum_slices16(const float4 *__restrict__ part, int nb, int E4,
+                                                      float4 *__restrict__ out) {
+  __shared__ float4 red[16 * 64];
+  sum_slices16(part, nb, E4, out, blockIdx.x, red);
 }
 
 // The first `cols` columns of `pitch`-wide rows: out[r * cols + c] = sum over b
@@ -1072,8 +1083,15 @@ void sum_partials(hipStream_t st, const float *part, int nb, int E, float *out) 
                        reinterpret_cast<const float4 *>(part), nb, E4, reinterpret_cast<float4 *>(out));
     return;
   }
-  if (E >= 16 * 2048 && vec) {
+  if (E >= 128 * 2048 && vec) {
     hipLaunchKernelGGL(k_sum_partials_vec, dim3((E4 + 63) / 64), dim3(64), 0, st,
+                       reinterpret_cast<const float4 *>(part), nb, E4, reinterpret_cast<float4 *>(out));
+    return;
+  }
+  // (from 256 partials on the sixteen slices are long enough to take more
+  // workgroups of one e per thread: 256 of 36,864 6.8 us, 9.0 as k_sum_slices16)
+  if (E >= 16 * 2048 && nb < 256 && vec) {
+    hipLaunchKernelGGL(k_sum_slices16, dim3((E4 + 63) / 64), dim3(256), 0, st,
                        reinterpret_cast<const float4 *>(part), nb, E4, reinterpret_cast<float4 *>(out));
     return;
   }

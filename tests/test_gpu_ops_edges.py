@@ -2,8 +2,8 @@
 and bars of test_gpu_ops_bf16: 3x3 convolutions whose rows come from a halo in
 LDS (128- and 256-row tiles with a remainder, odd sides, tiles across images,
 the widest image whose halo fits and the first that does not, 7 x 7 of 512
-channels), products of one k slice, partial sums around the 16-slice and the
-4-column rules, and batch-norm sums of few and many rows and odd channel
+channels), products of one k slice, partial sums around the rules on slices, columns
+and counts, and batch-norm sums of few and many rows and odd channel
 counts."""
 import numpy as np
 import pytest
@@ -39,8 +39,11 @@ def test_one_slice_product(m, monkeypatch):
     base.test_gemm_1x1_dgrad("one_slice", "addmask")
 
 
-@pytest.mark.parametrize("nb", [1, 16, 17, 32, 56])
-@pytest.mark.parametrize("count", [32768, 36866, 40004])
+SUMS = [(nb, count) for count in (32768, 36866, 40004) for nb in (1, 16, 17, 32, 56)]
+SUMS += [(255, 32772), (256, 32772), (40, 262140), (40, 262144), (19, 262146), (70, 300004)]
+
+
+@pytest.mark.parametrize("nb,count", SUMS)
 def test_sum_partials(nb, count):
     K = base._K()
     print(f"[op sum partials] {nb} x {count}", flush=True)
