@@ -34,8 +34,9 @@
 //             2 W + 2 of them, so they are loaded into LDS once with all their
 //             channels and each tap's operands are read from there, W kh + kw
 //             pixels further on (zeros from a zero row outside the image); only
-//             the weights pass through the ring.  A tile then loads 1.2 - 2.3
-//             times its own rows instead of nine times
+//             the weights pass through the ring.  A tile then loads 1 + (2 W +
+//             2) / BM times its own rows (at most 2.94, by the LDS a halo may take)
+//             instead of nine times
 // Out-of-image taps read zero.
 //
 // Block = 4 or 8 wavefronts (256 or 512 threads) in a WM x WN grid; each wavefront owns a
@@ -1211,13 +1212,16 @@ void launch_epi(const Args &a, int epi, int splits, hipStream_t s) {
   // 3x3 convolutions of stride 1 whose halo fits: tiles of 128 or 256 rows
   // (forward / data gradient with its sums, batch 32: 56 x 56 x 64 22.1 / 28.1 us
   // gathered, 21.0 / 24.8 from a halo; 28 x 28 x 128 17.2 / 23.1 and 16.3 /
-  // 21.5), and the forward of 64 x 64 tiles with eight wavefronts (7 x 7 x 512
-  // 24.4 and 23.4).  The other 64-row tiles are bound by their operand reads and
-  // barriers, not by loads: 14 x 14 x 256 forward 19.5 both ways, the data
-  // gradients of 14 x 14 and 7 x 7 23.4 and 28.5 gathered, 24.1 and 32.5 so.
+  // 21.5; batch 4, 123 x 123 x 64, where the halo is 2.9 times the tile's own
+  // rows, 14.1 / 18.9 and 13.6 / 17.5), and the forward of 64 x 64 tiles with
+  // eight wavefronts from 512 channels on (7 x 7 x 512 24.4 and 23.4; of 256
+  // channels batch 16, 14 x 14 13.3 and 13.9, batch 4, 28 x 28 13.1 and 13.7).
+  // The other 64-row tiles are bound by their operand reads and barriers, not by
+  // loads: 14 x 14 x 256 forward 19.5 both ways, the data gradients of 14 x 14
+  // and 7 x 7 23.4 and 28.5 gathered, 24.1 and 32.5 so.
   if constexpr (direct && (GA == GA_FWDT || GA == GA_DGRADT) &&
                 (BM >= 128 || (GA == GA_FWDT && BM == 64 && WM * WN == 8))) {
-    if (a.R == 3 && a.S == 1 && a.P == 1 && a.H == a.Ho && a.W == a.Wo && splits == 1 &&
+    if (a.R == 3 && a.S == 1 && a.P == 1 && a.H == a.Ho && a.W == a.Wo && splits == 1 && (BM > 64 || a.cshift >= 9) &&
         (int64_t(BM + 2 * a.W + 2) << (a.cshift + 1)) + std::max(1024, 2 << a.cshift) <= halo_bytes(BM, WM * WN)) {
       launch_epi_s<BM, BN, WM, WN, AK, BK, TA, GA, GB, SAFE, BM + BN == 256 && WM * WN == 4 ? 8 + 2 : 8 + 3>(a, epi, splits, s);
       return;
