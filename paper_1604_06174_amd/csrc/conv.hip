@@ -533,6 +533,35 @@ struct SpecUse {
   int RB = 0, BN = 0;
 };
 
+// The stride-1 convolutions with C inputs and outputs on W x W pixels whose
+// gradients have kernels of their own: rows per workgroup of the data gradient,
+// rows per tile and tiles per workgroup of the weight gradient (0: pixel ranges).
+template <int C, int W>
+struct GradTiles {
+  static constexpr int DG = 0;  // none
+};
+template <>
+struct GradTiles<16, 32> {
+  static constexpr int DG = 4, WG = 4, TPB = 2;
+};
+template <>
+struct GradTiles<32, 16> {
+  static constexpr int DG = 4, WG = 4, TPB = 2;
+};
+template <>
+struct GradTiles<64, 8> {
+  static constexpr int DG = 8, WG = 0, TPB = 0;
+};
+
+// GradTiles' DG at run time (0: none)
+int grad_rows(int S, int H, int W, int C, int J) {
+  if (S != 1 || H != W || C != J) return 0;
+  if (C == 16 && W == 32) return GradTiles<16, 32>::DG;
+  if (C == 32 && W == 16) return GradTiles<32, 16>::DG;
+  if (C == 64 && W == 8) return GradTiles<64, 8>::DG;
+  return 0;
+}
+
 // One row of the specialisation table; returns whether it matches the launch.
 template <int C, int J, int W, int S, int MODE, int EPI, int RB, int BN>
 bool spec_try(const ConvArgs &a, int mode, int s, int epi, hipStream_t st, bool launch, SpecUse *u) {
@@ -550,11 +579,10 @@ bool spec_try(const ConvArgs &a, int mode, int s, int epi, hipStream_t st, bool 
 // The CIFAR-shaped network's convolutions: 16/32/64 channels at 32/16/8 pixels.
 bool spec_dispatch(const ConvArgs &a, int mode, int s, int epi, hipStream_t st, bool launch, SpecUse *u) {
   constexpr int F = CONV_FWD, D = CONV_DGRAD;
-  constexpr int STATS = CONV_EPI_STATS, MASK = CONV_EPI_MASK, SC1 = CONV_EPI_SC1, SC2 = CONV_EPI_SC2,
-                MST = CONV_EPI_MASKSTATS, STORE = CONV_EPI_STORE;
+  constexpr int STATS = CONV_EPI_STATS, SC2 = CONV_EPI_SC2, STORE = CONV_EPI_STORE;
   // rows per workgroup and output channels per workgroup as measured best on
   // MI355X for these shapes (the forward without statistics: a re-run that
-  // reuses them)
+  // reuses them); the stride-1 data gradients run in conv3x3_bwd
   return spec_try<16, 16, 32, 1, F, STATS, 4, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<16, 16, 32, 1, F, STORE, 4, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<16, 32, 16, 2, F, STORE, 4, 32>(a, mode, s, epi, st, launch, u) ||
@@ -565,15 +593,6 @@ bool spec_dispatch(const ConvArgs &a, int mode, int s, int epi, hipStream_t st, 
          spec_try<32, 32, 16, 1, F, STATS, 8, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<32, 64, 8, 2, F, STATS, 8, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<64, 64, 8, 1, F, STATS, 8, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<16, 16, 32, 1, D, MASK, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<32, 32, 16, 1, D, MASK, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<64, 64, 8, 1, D, MASK, 8, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<16, 16, 32, 1, D, MST, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<32, 32, 16, 1, D, MST, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<64, 64, 8, 1, D, MST, 8, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<16, 16, 32, 1, D, SC1, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<32, 32, 16, 1, D, SC1, 4, 16>(a, mode, s, epi, st, launch, u) ||
-         spec_try<64, 64, 8, 1, D, SC1, 8, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<32, 16, 32, 2, D, SC2, 4, 16>(a, mode, s, epi, st, launch, u) ||
          spec_try<64, 32, 16, 2, D, SC2, 4, 16>(a, mode, s, epi, st, launch, u);
 }
@@ -940,9 +959,9 @@ bool wgs_try(const WgArgs &a, hipStream_t st, bool launch, WgUse *u) {
 // CIFAR-shaped network's shapes (batch 128, weight gradient + partial sums)
 bool wgs_dispatch(const WgArgs &a, hipStream_t st, bool launch, WgUse *u) {
   return wgs_try<3, 16, 32, 1, 8, 1>(a, st, launch, u) ||
-         wgs_try<16, 16, 32, 1, 4, 2>(a, st, launch, u) ||
+         wgs_try<16, 16, 32, 1, GradTiles<16, 32>::WG, GradTiles<16, 32>::TPB>(a, st, launch, u) ||
          wgs_try<16, 32, 16, 2, 4, 2>(a, st, launch, u) ||
-         wgs_try<32, 32, 16, 1, 4, 2>(a, st, launch, u) ||
+         wgs_try<32, 32, 16, 1, GradTiles<32, 16>::WG, GradTiles<32, 16>::TPB>(a, st, launch, u) ||
          wgs_try<32, 64, 8, 2, 4, 2>(a, st, launch, u);
 }
 
@@ -1188,36 +1207,37 @@ void launch_mode(const ConvArgs &a, int mode, int S, int epi, size_t lds, dim3 g
 // workgroups take longer); each does what its own kernel does, so the bits are
 // the same.  Batch 128, the two launches and the one: 16 channels 28.6 -> 23.7
 // us, 32 27.4 -> 23.6, 64 30.5 -> 25.5 (with the first batch norm's sums).
-// WG_RB > 0: tiles of wgrad_s; 0: pixel ranges of conv3x3_wgrad.
-template <int C, int W, int RB, int WG_RB, int WG_TPB>
+template <int C, int W>
 constexpr size_t pair_lds() {
-  constexpr size_t d = spec_lds<C, C, W, 1, CONV_DGRAD, RB, 16>();
-  constexpr size_t g = WG_RB ? wgs_lds<C, C, W, 1, WG_RB ? WG_RB : 1>() : wgrad_lds(C);
+  typedef GradTiles<C, W> T;
+  constexpr size_t d = spec_lds<C, C, W, 1, CONV_DGRAD, T::DG, 16>();
+  constexpr size_t g = T::WG ? wgs_lds<C, C, W, 1, T::WG ? T::WG : 1>() : wgrad_lds(C);
   return d > g ? d : g;
 }
 
-template <int C, int W, int EPI, int RB, int WG_RB, int WG_TPB, int WPE>
+template <int C, int W, int EPI, int WPE>
 __global__ __launch_bounds__(256, WPE) void k_conv3x3_bwd(ConvArgs a, WgArgs w, int gw, int nw, int gd) {
-  __shared__ __align__(16) float smem[pair_lds<C, W, RB, WG_RB, WG_TPB>() / 4];
+  typedef GradTiles<C, W> T;
+  __shared__ __align__(16) float smem[pair_lds<C, W>() / 4];
   const int id = blockIdx.x;
   if (id < nw) {
-    if constexpr (WG_RB > 0) wgrad_s_tiles<C, C, W, 1, WG_RB, WG_TPB>(w, id % gw, id / gw, smem);
+    if constexpr (T::WG > 0) wgrad_s_tiles<C, C, W, 1, T::WG, T::TPB>(w, id % gw, id / gw, smem);
     else conv3x3_wgrad_range<C, C, W, W, 1>(w, id % gw, id / gw, smem);
   } else {
-    conv3x3s_tile<C, C, W, 1, CONV_DGRAD, EPI, RB, 16>(a, (id - nw) % gd, (id - nw) / gd, gd, smem);
+    conv3x3s_tile<C, C, W, 1, CONV_DGRAD, EPI, T::DG, 16>(a, (id - nw) % gd, (id - nw) / gd, gd, smem);
   }
 }
 
-// Launches the pair if it is one of these shapes; *gw is then the number of
-// weight-gradient partials.  Same tiles as the separate kernels.
-template <int C, int W, int EPI, int RB, int WG_RB, int WG_TPB, int WPE>
+// Launches the pair if it is this shape; *gw is then the number of
+// weight-gradient partials.
+template <int C, int W, int EPI, int WPE>
 static bool pair_try(const ConvArgs &a, const WgArgs &w, int epi, hipStream_t st, int *gw) {
   if (epi != EPI || a.C != C || a.J != C || a.W != W || a.H != W) return false;
-  static_assert(pair_lds<C, W, RB, WG_RB, WG_TPB>() <= 96 * 1024, "LDS");
-  const int gd = a.N * (W / RB), nd = gd * (C / 16);
+  static_assert(pair_lds<C, W>() <= 96 * 1024, "LDS");
+  const int gd = conv3x3_blocks(CONV_DGRAD, 1, a.N, W, W, C, C), nd = gd * (C / 16);
   *gw = conv3x3_wgrad_blocks(1, a.N, W, W, C, C);
   const int nw = *gw * ((9 * C + WG_NB - 1) / WG_NB);
-  launch_timed((k_conv3x3_bwd<C, W, EPI, RB, WG_RB, WG_TPB, WPE>), dim3(nw + nd), dim3(256), 0, st, a, w, *gw, nw, gd);
+  launch_timed((k_conv3x3_bwd<C, W, EPI, WPE>), dim3(nw + nd), dim3(256), 0, st, a, w, *gw, nw, gd);
   return true;
 }
 
@@ -1234,11 +1254,13 @@ static ConvArgs shape_args(int mode, int S, int N, int H, int W, int C, int J) {
 
 int conv3x3_blocks(int mode, int S, int N, int H, int W, int C, int J) {
   SpecUse u;
-  // the statistics partials are indexed by blockIdx.x only (STATS in the
-  // forward, MASKSTATS in the data gradient)
-  if (spec_dispatch(shape_args(mode, S, N, H, W, C, J), mode, S,
-                    mode == CONV_FWD ? CONV_EPI_STATS : CONV_EPI_MASKSTATS, nullptr, false, &u))
+  // the statistics partials are indexed by the row tile only (STATS in the
+  // forward, MASKSTATS in the stride-1 data gradient)
+  if (mode == CONV_DGRAD) {
+    if (const int rows = grad_rows(S, H, W, C, J)) return N * (H / rows);
+  } else if (spec_dispatch(shape_args(mode, S, N, H, W, C, J), mode, S, CONV_EPI_STATS, nullptr, false, &u)) {
     return N * ((H + u.RB - 1) / u.RB);
+  }
   return N * conv_tile(mode, S, H, W, C, J).rblk;
 }
 
@@ -1267,6 +1289,8 @@ void conv3x3(hipStream_t st, int mode, int S, int epi, const float *X, const flo
              const float *tb, float *rout) {
   if (epi == CONV_EPI_MASKSTATS && (mode != CONV_DGRAD || !tst || !tg || !tb || !stats || !E0))
     fail(CKPT_E_INVALID, "conv3x3: MASKSTATS needs a data gradient, the mask operand, its statistics and stats");
+  if ((epi == CONV_EPI_MASKSTATS || epi == CONV_EPI_SC1) && grad_rows(S, H, W, C, J))
+    fail(CKPT_E_INVALID, "conv3x3: this shape's data gradient runs in conv3x3_bwd");
   if (rout && (mode != CONV_FWD || S != 1 || !tst || (C & 3) != 0))
     fail(CKPT_E_INVALID, "conv3x3: the transformed input is stored only by a stride-1 forward with a transform");
   Tile t = conv_tile(mode, S, H, W, C, J);
@@ -1324,9 +1348,9 @@ bool conv3x3_bwd(hipStream_t st, int epi, const float *DY, const float *Wt, floa
                  x_raw ? tst : nullptr, tg, tb};
   constexpr int MST = CONV_EPI_MASKSTATS, SC1 = CONV_EPI_SC1;
   int gw = 0;
-  const bool ok = pair_try<16, 32, MST, 4, 4, 2, 3>(a, w, epi, st, &gw) || pair_try<16, 32, SC1, 4, 4, 2, 3>(a, w, epi, st, &gw) ||
-                  pair_try<32, 16, MST, 4, 4, 2, 4>(a, w, epi, st, &gw) || pair_try<32, 16, SC1, 4, 4, 2, 4>(a, w, epi, st, &gw) ||
-                  pair_try<64, 8, MST, 8, 0, 0, 2>(a, w, epi, st, &gw) || pair_try<64, 8, SC1, 8, 0, 0, 2>(a, w, epi, st, &gw);
+  const bool ok = pair_try<16, 32, MST, 3>(a, w, epi, st, &gw) || pair_try<16, 32, SC1, 3>(a, w, epi, st, &gw) ||
+                  pair_try<32, 16, MST, 4>(a, w, epi, st, &gw) || pair_try<32, 16, SC1, 4>(a, w, epi, st, &gw) ||
+                  pair_try<64, 8, MST, 2>(a, w, epi, st, &gw) || pair_try<64, 8, SC1, 2>(a, w, epi, st, &gw);
   if (ok) *sum = {part, gw, 9 * C * C, dW};
   return ok;
 }

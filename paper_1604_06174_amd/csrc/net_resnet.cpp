@@ -318,13 +318,13 @@ class ResNetBasic : public Net {
     bn_backward_apply(c.s, np, k.cout, Pb, nullptr, c1, st1, P(c, k.g1), sums, Qb);
     c.launches += 5;
     // conv1: data gradient plus the shortcut's gradient, weight gradient
-    if (dxv && k.stride == 1 && k.cin == k.cout) {
+    if (dxv && k.stride == 1) {
       conv_bwd(c, CONV_EPI_SC1, Qb, P(c, k.w1), static_cast<float *>(dxv), x, G(c, k.w1), ho, k.cout, g, y, nullptr,
                nullptr, nullptr, false);
       return;
     }
     if (dxv) {
-      conv(c, CONV_DGRAD, k.stride, k.stride == 1 ? CONV_EPI_SC1 : CONV_EPI_SC2, Qb, P(c, k.w1),
+      conv(c, CONV_DGRAD, k.stride, CONV_EPI_SC2, Qb, P(c, k.w1),
            static_cast<float *>(dxv), k.hin, k.hin, ho, ho, k.cout, k.cin, g, y, ho, ho, k.cout, ho,
            k.cin, k.cout);
       c.launches += 1;
