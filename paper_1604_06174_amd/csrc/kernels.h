@@ -44,8 +44,8 @@ void gemm_f32(hipStream_t s, int M, int N, int K, const float *A, int lda, bool 
 int mlp_row_blocks(int rows);
 int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const float *x, const float *W,
             float *dx, float *dW, float *db, float *pdb);
-// column sums of g [rows, cols] in the order of mlp_bwd's
-void mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb);
+// column sums of g [rows, cols] in the order of mlp_bwd's; returns the launches
+int mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb);
 // the same through partial sums of 16-row blocks (pdb), for many rows; g
 // counts where z > 0 when z is given
 void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb);

@@ -390,11 +390,13 @@ int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const f
   return db_here ? 1 : 3;
 }
 
-void mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb) {
-  if (rows <= kMaxDbRows)
+int mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb) {
+  if (rows <= kMaxDbRows) {
     hipLaunchKernelGGL(k_colsum, dim3((cols + 31) / 32), dim3(512), 0, s, rows, cols, g, db);
-  else
-    mlp_colsum_long(s, rows, cols, g, nullptr, db, pdb);
+    return 1;
+  }
+  mlp_colsum_long(s, rows, cols, g, nullptr, db, pdb);
+  return 2;
 }
 
 }  // namespace ckpt

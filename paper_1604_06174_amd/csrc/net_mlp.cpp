@@ -105,8 +105,9 @@ class MlpNet : public Net {
       if (hipMemcpyAsync(y, c.input, size_t(t) * 4, hipMemcpyDeviceToDevice, c.s) != hipSuccess)
         fail(CKPT_E_HIP, "train_step_graph: input copy failed");
     } else if (v == 3 * n + 1) {
-      mse_head(c.s, t, static_cast<const float *>(ins[0]), static_cast<const float *>(c.target), y,
-               partials(c), reinterpret_cast<float *>(c.ks));
+      c.launches += mse_head(c.s, t, static_cast<const float *>(ins[0]), static_cast<const float *>(c.target), y,
+                             partials(c), reinterpret_cast<float *>(c.ks));
+      return;
     } else {
       const int i = (v - 1) / 3, k = (v - 1) % 3;
       const float *x = static_cast<const float *>(ins[0]);

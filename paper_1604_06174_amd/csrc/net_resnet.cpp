@@ -514,9 +514,8 @@ class ResNetBasic : public Net {
         const float *x = static_cast<const float *>(ins[0]);
         gemm_f32(c.s, N, d.cin, K, dy, K, false, P(c, hw), K, true, o, d.cin, GEMM_EPI_STORE);
         gemm_f32(c.s, d.cin, K, N, x, d.cin, true, dy, K, false, G(c, hw), K, GEMM_EPI_STORE);
-        mlp_colsum(c.s, N, K, dy, G(c, hb), ksf(c, ks_fcpart));
-        c.launches += 3;
-        break;
+        c.launches += 2 + mlp_colsum(c.s, N, K, dy, G(c, hb), ksf(c, ks_fcpart));
+        return;
       }
       case ND_LOSS:  // the loss node's output is dL/d(logits) already
         ew_copy(c.s, int64_t(N) * K, static_cast<const float *>(yv), o);

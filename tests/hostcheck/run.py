@@ -353,9 +353,13 @@ def dry_step(cfg, plans, static=False, graph_step=False, record=False):
             params, grads = LIB.hc_alloc(pb.value, b"params"), LIB.hc_alloc(pb.value, b"grads")
             b = Batch(LIB.hc_alloc(ib, b"input"), LIB.hc_alloc(tb, b"target"))
             work = LIB.hc_alloc(ws.value, b"workspace")
-            loss = C.c_float()
+            loss, st, before = C.c_float(), Stats(), counters()
             ok(LIB.train_step_graph(net, params, grads, C.byref(b), gp, work, ws.value, None, None,
-                                    C.byref(loss), None, None), f"{name}: train_step_graph")
+                                    C.byref(loss), None, C.byref(st)), f"{name}: train_step_graph")
+            seen = counters()[0] - before[0]
+            # the input reaches its node as a device copy, counted with the kernels
+            check(seen + 1 == st.kernel_launches,
+                  f"{name}: graph step launches seen {seen} + 1 vs reported {st.kernel_launches}")
             LIB.graph_plan_free(gp)
     LIB.net_destroy(net)
 
@@ -366,6 +370,8 @@ ALL = [(PL.NONE, 0, 0), (PL.SQRT, 0, 0), (PL.SQRT, 0, PL.FLAG_KEEP_LAST), (PL.GR
 
 def dry_runs(quick):
     small = [dict(kind="mlp", depth=9, width=72, batch=37, name="mlp small"),
+             dict(kind="mlp", depth=3, width=40, batch=9, name="mlp one-workgroup head"),
+             dict(kind="mlp", depth=3, width=8, batch=1025, name="mlp many rows"),
              dict(kind="resnet_basic", blocks_per_stage=2, base=8, batch=3, image=16, classes=7,
                   name="cifar small"),
              dict(kind="resnet_basic", blocks_per_stage=2, base=8, batch=3, image=16, classes=7,
