@@ -7,6 +7,7 @@
 // E[x^2] - E[x]^2.
 #include <hip/hip_runtime.h>
 
+#include "common.h"
 #include "kernels.h"
 #include "sum_slices.h"
 
@@ -704,13 +705,13 @@ void bn_finalize_fwd(hipStream_t s, const double *part, int nb, int J, int64_t m
 void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *sums,
                      float *dgamma, float *dbeta, bool channel_major, const SumJob &sum) {
   const int E4 = sum.E / 4;
-  if (E4 && channel_major) {
+  if (E4 && !channel_major) fail(CKPT_E_INVALID, "bn_finalize_bwd: a sum goes with channel-major partials");
+  if (E4) {
     const int g = E4 >= SUM_SLICES16_E4 ? (E4 + 63) / 64 : (E4 + 3) / 4;
     hipLaunchKernelGGL(k_bn_finalize_sum, dim3(J + g), dim3(256), 0, s, part, nb, J, double(m), sums, dgamma, dbeta,
                        reinterpret_cast<const float4 *>(sum.part), sum.nb, E4, reinterpret_cast<float4 *>(sum.out));
     return;
   }
-  if (E4) sum_partials(s, sum.part, sum.nb, sum.E, sum.out);
   bn_finalize<false>(s, part, nb, J, m, sums, dgamma, dbeta, channel_major);
 }
 

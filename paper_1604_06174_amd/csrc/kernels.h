@@ -150,7 +150,8 @@ void softmax_ce_rows(hipStream_t s, int N, int K, const float *L, const int *lab
                      float *lossn, float *loss);
 // sums[0..J) = mean(ds), sums[J..2J) = mean(ds xhat), dgamma, dbeta from the
 // backward partials (sum ds, sum ds xhat) of nb workgroups over m values, in
-// either layout (fp32 backward partials: channel-major; bf16: block-major)
+// either layout (fp32 backward partials: channel-major; bf16: block-major); sum
+// goes with the channel-major one
 void bn_finalize_bwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *sums,
                      float *dgamma, float *dbeta, bool channel_major, const SumJob &sum = {});
 
