@@ -3,8 +3,9 @@
 // that a deep chain stays trainable); head = mean squared error.
 //
 // Static layout per unit: boundary b = [B, D] f32; saved internals a = the
-// pre-activation z [B, D]; gradient scratch q = one [B, D] tensor (the masked
-// gradient dr, which the backward forms as it reads g and z).
+// pre-activation z [B, D]; gradient scratch q = one [B, D] tensor.  The backward
+// masks g as it reads it and stores nothing there; the tensor stays in the
+// layout, whose sizes and peaks budgets and stored plans were made for.
 #include "kernels.h"
 #include "net.h"
 
