@@ -26,6 +26,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "launch.h"
 
 namespace ckpt {
 namespace {
@@ -553,7 +554,7 @@ void lstm_step_fwd(hipStream_t s, int B, int H, int E, const void *x, const void
   // batches of at most 16 rows take 16-row tiles; a short k (at most 16 steps
   // of 32) four wavefronts instead of sixteen
 #define CKPT_STEP_FWD(RT, NW)                                                                          \
-  hipLaunchKernelGGL((k_lstm_step_fwd<RT, NW>), dim3((B + 16 * RT - 1) / (16 * RT) * (H / 8)), dim3(64 * NW), 0, \
+  launch_timed(k_lstm_step_fwd<RT, NW>, dim3((B + 16 * RT - 1) / (16 * RT) * (H / 8)), dim3(64 * NW), 0, \
                      s, B, H, E, K2, xp, hp, wp, bias, c_prev, gates, ho, c_out)
   const bool few = E + H <= 512;  // of the shape, not of the step: the same order with and without h
   if (B <= 16) {
@@ -584,7 +585,7 @@ void lstm_step_bwd(hipStream_t s, int B, int H, const void *dzn, const void *w,
                    float *dc_prev, void *hp_copy, void *hc_copy, float *dbp) {
   const dim3 grid(lstm_step_row_blocks(B) * ((H + 15) / 16));
 #define CKPT_STEP_BWD(NW)                                                                             \
-  hipLaunchKernelGGL(k_lstm_step_bwd<NW>, grid, dim3(64 * NW), 0, s, B, H, static_cast<const __bf16 *>(dzn), \
+  launch_timed(k_lstm_step_bwd<NW>, grid, dim3(64 * NW), 0, s, B, H, static_cast<const __bf16 *>(dzn), \
                      static_cast<const __bf16 *>(w), hpart, ns, slice, dc_in, gates, c_t, c_prev, \
                      static_cast<const __bf16 *>(h_prev), static_cast<const __bf16 *>(h_t),           \
                      static_cast<__bf16 *>(dz), dc_prev, static_cast<__bf16 *>(hp_copy),              \

@@ -140,7 +140,7 @@ class LstmNet : public Net {
     nb = int(std::min<uint64_t>(std::min(C, HG), (buf_floats - fixed) / batched));
     k_buf = take(buf_floats * 4);
     ks_bytes = off;
-    timed_family = "k_gemm_bf16";
+    timed_family = "k_gemm_bf16 and k_lstm_step";
   }
 
   int row_blocks() const { return step_bwd ? lstm_step_row_blocks(B) : lstm_point_row_blocks(B); }
@@ -197,7 +197,11 @@ class LstmNet : public Net {
     const float *c_prev = i > 0 ? reinterpret_cast<const float *>(x + hb) : nullptr;
     float *gates = reinterpret_cast<float *>(sv), *c_out = reinterpret_cast<float *>(y + hb);
     if (step_fwd) {
+      // operands once; c_{t-1} (from step 1 on), the gates, c and h once
+      const double k = double(E) + (i > 0 ? H : 0), bh = double(B) * H;
+      timer.begin(c.s);
       lstm_step_fwd(c.s, B, H, E, xt, i > 0 ? x : nullptr, K(c, k_wcat), P(c, pb), c_prev, gates, y, c_out);
+      timer.end(c.s, 8.0 * bh * k, 2.0 * (B * k + 4.0 * H * k) + (i > 0 ? 26.0 : 22.0) * bh);
       c.launches += 1;
       return;
     }
@@ -310,9 +314,14 @@ class LstmNet : public Net {
     char *hp = X(c, x_hp) + row * H * 2, *hc = X(c, x_hc) + row * H * 2;
     float *dbp = Kf(c, k_dbp) + size_t(t_end - 1 - i) * rb * 4 * H;
     if (step_bwd) {
+      // dz_{t+1} and W_h once (none at the last step), dh's head part once; the
+      // gates, c, c_{t-1}, dc and h's read, dz, dc_{t-1} and h's copies written
+      const double k = last ? 0.0 : 4.0 * H, bh = double(B) * H;
+      timer.begin(c.s);
       lstm_step_bwd(c.s, B, H, dzn, K(c, k_wob) + size_t(H) * V * 2, Kf(c, k_buf) + size_t(i - c.ready_lo) * B * H,
                     s_head, int64_t(c.ready_hi - c.ready_lo) * B * H, dc_in, gates, c_t, c_prev, h_prev, y, dz, dc_prev,
                     hp, hc, dbp);
+      timer.end(c.s, 2.0 * bh * k, 2.0 * k * (B + H) + (4 + 16 + 12 + 4 + 8 + 4 + 4) * bh);
     } else {
       const char *dl = X(c, x_dl) + row * V * 2;
       if (last) {

@@ -29,3 +29,24 @@ EDGES = {
 def test_lstm_step_edges(case, monkeypatch):
     monkeypatch.setitem(base.CASES, case, dict(EDGES[case], kind="lstm", seed=75))
     base.test_lstm_step_parity_all_modes(case)
+
+
+def test_kernel_timer_covers_the_step_kernels():
+    """The timed family's operations are those of every product of the step: the
+    gates', the recurrent part of dh, the heads' three and the weight gradients."""
+    import synth
+    from paper_1604_06174_amd import ckpt as K
+    from paper_1604_06174_amd.workload import GpuStep
+    cfg = dict(base.CASES["mid"])
+    T, B, E, H, V = (cfg[k] for k in ("T", "batch", "input", "hidden", "vocab"))
+    d = synth.make(cfg)
+    step = GpuStep(cfg, d["params"], d["input"], d["target"])
+    step.net.timing_enable(True)
+    step.run(step.plan(K.NONE))
+    kt = step.net.timing_read()
+    step.net.timing_enable(False)
+    gates = T * 8 * B * H * E + (T - 1) * 8 * B * H * H
+    heads = 3 * T * 2 * B * V * H
+    weights = T * 8 * B * H * (E + H)
+    assert kt["flops"] == gates + (T - 1) * 8 * B * H * H + heads + weights
+    assert kt["ms"] > 0 and kt["launches"] >= 2 * T
