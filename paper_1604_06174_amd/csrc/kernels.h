@@ -47,8 +47,12 @@ int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const f
 // column sums of g [rows, cols] in the order of mlp_bwd's; returns the launches
 int mlp_colsum(hipStream_t s, int rows, int cols, const float *g, float *db, float *pdb);
 // the same through partial sums of 16-row blocks (pdb), for many rows; g
-// counts where z > 0 when z is given
-void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb);
+// counts where z > 0 when z is given, and what counts is stored to dr when given
+// (two launches)
+void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb,
+                     float *dr = nullptr);
+// the shapes for which mlp_bwd is faster than its products one by one (gemm_f32)
+bool mlp_bwd_wins(int B, int D);
 
 // Mean-squared-error head: loss_out[0] = sum((y-t)^2)/count, g = 2 (y-t)/count;
 // part is workspace of mse_blocks(count) floats.  Returns the launches.

@@ -9,11 +9,12 @@ namespace ckpt {
 namespace {
 
 // Workgroup = 64 columns x 4 row groups over a block of 16 rows (blockIdx.y)
-// of g (of g where z > 0 when z is given): the workgroup's column sums over
-// its rows, ((s0 + s1) + s2) + s3 with s_j = rows j, j+4, .. in order, go to
-// pdb[blockIdx.y][cols].
+// of g (of g where z > 0 when z is given, stored to dr when that is): the
+// workgroup's column sums over its rows, ((s0 + s1) + s2) + s3 with s_j = rows
+// j, j+4, .. in order, go to pdb[blockIdx.y][cols].
 __global__ __launch_bounds__(256) void k_colsum_part(int rows, int cols, const float *__restrict__ g,
-                                                     const float *__restrict__ z, float *__restrict__ pdb) {
+                                                     const float *__restrict__ z, float *__restrict__ dr,
+                                                     float *__restrict__ pdb) {
   __shared__ float part[4][64];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + tx, r0 = blockIdx.y * 16 + ty;
@@ -29,7 +30,11 @@ __global__ __launch_bounds__(256) void k_colsum_part(int rows, int cols, const f
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (r0 + 4 * i < rows) s += zv[i] > 0.f ? gv[i] : 0.f;
+      if (r0 + 4 * i < rows) {
+        const float v = zv[i] > 0.f ? gv[i] : 0.f;
+        if (dr) dr[size_t(r0 + 4 * i) * cols + n] = v;
+        s += v;
+      }
   }
   part[ty][tx] = s;
   __syncthreads();
@@ -132,9 +137,10 @@ int ew_blocks(int64_t n) {
 
 int mlp_row_blocks(int rows) { return (rows + 15) / 16; }
 
-void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb) {
+void mlp_colsum_long(hipStream_t s, int rows, int cols, const float *g, const float *z, float *db, float *pdb,
+                     float *dr) {
   const int R = mlp_row_blocks(rows);
-  hipLaunchKernelGGL(k_colsum_part, dim3((cols + 63) / 64, R), dim3(256), 0, s, rows, cols, g, z, pdb);
+  hipLaunchKernelGGL(k_colsum_part, dim3((cols + 63) / 64, R), dim3(256), 0, s, rows, cols, g, z, dr, pdb);
   hipLaunchKernelGGL(k_colsum_rows, dim3((cols + 255) / 256), dim3(256), 0, s, R, cols, pdb, db);
 }
 

@@ -5,7 +5,7 @@
 // None of the three needs another, so one launch runs them side by side.  As
 // four launches (dr with partial column sums, their sum, dW, dx) a block of 64 x
 // 256 took 13.6 us and one of 256 x 1024 30 us, most of it launches and chips
-// left idle by each small product in turn; together they take 5.8 and 23 us.
+// left idle by each small product in turn; together they take 6.2 and 24 us.
 // dr is not stored: the mask is applied to g as it is read.
 //
 // Workgroup = 8 wavefronts; each wavefront computes a 32 x 32 tile over its
@@ -334,21 +334,23 @@ __global__ __launch_bounds__(512) void k_colsum(int rows, int cols, const float 
   db_block(rows, cols, g, nullptr, db, blockIdx.x * 32, part);
 }
 
-// n_wg workgroups for dW (wg), n_dg for dx (dg), the rest for db.  MASK: dr =
-// (z > 0 ? g : 0) and dx = g + dr W^T; else g is dr itself and dx = dr W^T.
+// n_first workgroups for db, n_wg for dW (wg), n_dg for dx (dg), the rest for db.
+// MASK: dr = (z > 0 ? g : 0) and dx = g + dr W^T; else g is dr itself and dx = dr
+// W^T.
 template <int KSW, int KSD, bool MASK, bool VEC>
-__global__ __launch_bounds__(64 * NW) void k_gemm_f32_mlp_bwd(GemmArgs wg, GemmArgs dg, const float *z, int n_wg,
-                                                              int n_dg, float *db) {
+__global__ __launch_bounds__(64 * NW) void k_gemm_f32_mlp_bwd(GemmArgs wg, GemmArgs dg, const float *z, int n_first,
+                                                              int n_wg, int n_dg, float *db) {
   constexpr int NS = VEC ? 3 : 2, ST = NW * (MASK ? 3 : 2) * OPB;
   __shared__ __align__(1024) unsigned char s0[ST], s1[ST], s2[NS > 2 ? ST : 1];
-  const int id = blockIdx.x;
-  if (id < n_wg)
+  const int id = int(blockIdx.x) - n_first;
+  if (id < 0 || id >= n_wg + n_dg)
+    db_block(wg.K, wg.N, wg.B, MASK ? z : nullptr, db, (id < 0 ? id + n_first : id - n_wg - n_dg) * 32,
+             reinterpret_cast<float *>(s0));
+  else if (id < n_wg)
     tile_block<KSW, NS, MASK ? 2 : 0, true, false, GEMM_EPI_STORE, VEC>(wg, z, xcd_run(id, n_wg), s0, s1, s2);
-  else if (id < n_wg + n_dg)
+  else
     tile_block<KSD, NS, MASK ? 1 : 0, false, true, MASK ? GEMM_EPI_ADD : GEMM_EPI_STORE, VEC>(
         dg, z, xcd_run(id - n_wg, n_dg), s0, s1, s2);
-  else
-    db_block(wg.K, wg.N, wg.B, MASK ? z : nullptr, db, (id - n_wg - n_dg) * 32, reinterpret_cast<float *>(s0));
 }
 
 // f(integral_constant<int, ks>) for ks in {1, 2, 4, 8}
@@ -364,6 +366,24 @@ inline bool al16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) =
 
 }  // namespace
 
+// The joint launch saves launches and idle compute units; its wavefronts share no
+// operands, which gemm_f32's tiles do.  Whole steps of 12 blocks (960 x 1024: 48)
+// without checkpoints, products one by one and joint, us (rows x width):
+//   joint      256 x 256 223 / 141, 2048 x 256 502 / 438, 4096 x 384 1052 / 989, 256 x
+//              512 257 / 222, 768 x 800 816 / 771, 512 x 960 699 / 666, 256 x 1024
+//              413 / 387, 960 x 1024 5181 / 4812, 256 x 1536 836 / 758, 128 x 1792
+//              570 / 563
+//   products   1024 x 500 502 / 563, 1024 x 700 820 / 916, 2048 x 800 1512 / 1781, 1024
+//              x 1024 1252 / 1336, 768 x 1280 1419 / 1495, 1536 x 1536 3598 / 4045, 256
+//              x 2048 1089 / 1121, 64 x 3072 852 / 963, 32 x 4096 1011 / 1300, 8192 x
+//              384 1650 / 1811
+// so: up to 2^30 multiplications per product; past 448 columns (where dW alone
+// fills the chip with gemm_f32's tiles) with fewer rows than columns, and of 2048
+// columns on never.
+bool mlp_bwd_wins(int B, int D) {
+  return int64_t(B) * D * D < (int64_t(1) << 30) && (D <= 448 || (D < 2048 && B < D));
+}
+
 int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const float *x, const float *W,
             float *dx, float *dW, float *db, float *pdb) {
   // 16-byte loads; W counts only when dx is formed, which any W allows
@@ -372,14 +392,18 @@ int mlp_bwd(hipStream_t s, int B, int D, const float *g, const float *z, const f
   const GemmArgs dg{B, D, D, g, D, W, D, dx, D, g, D, nullptr, nullptr, 0};
   const bool db_here = B <= kMaxDbRows;
   const Split sw = split_of(D, D, B), sd = split_of(B, D, D);
-  const int n_dg = dx ? sd.blocks : 0, n_db = db_here ? (D + 31) / 32 : 0;
+  // db's workgroups are chains of loads, one after another from 64 rows on: where
+  // they are long they start first, so that the products hide them (1024 x 512:
+  // 43 us with them last, 31 so; 256 x 1024 26.1 and 27.7)
+  const int n_dg = dx ? sd.blocks : 0, n_db = db_here ? (D + 255) / 256 * 8 : 0;  // (whole rounds of the XCDs)
+  const int n_first = B > 512 ? n_db : 0;
   if (!db_here) mlp_colsum_long(s, B, D, g, z, db, pdb);
   const dim3 grid(sw.blocks + n_dg + n_db);
   with_ks(sw.ks, [&](auto KSW) {
     with_ks(sd.ks, [&](auto KSD) {
       constexpr int kw = decltype(KSW)::value, kd = decltype(KSD)::value;
       const auto run = [&](auto kernel) {
-        launch_timed(kernel, grid, dim3(64 * NW), 0, s, wg, dg, z, sw.blocks, n_dg, db);
+        launch_timed(kernel, grid, dim3(64 * NW), 0, s, wg, dg, z, n_first, sw.blocks, n_dg, db);
       };
       if (z && vec) run(k_gemm_f32_mlp_bwd<kw, kd, true, true>);
       else if (z) run(k_gemm_f32_mlp_bwd<kw, kd, true, false>);

@@ -3,9 +3,8 @@
 // that a deep chain stays trainable); head = mean squared error.
 //
 // Static layout per unit: boundary b = [B, D] f32; saved internals a = the
-// pre-activation z [B, D]; gradient scratch q = one [B, D] tensor.  The backward
-// masks g as it reads it and stores nothing there; the tensor stays in the
-// layout, whose sizes and peaks budgets and stored plans were made for.
+// pre-activation z [B, D]; gradient scratch q = one [B, D] tensor (the masked
+// gradient dr, stored where the products run one by one).
 #include "kernels.h"
 #include "net.h"
 
@@ -53,16 +52,38 @@ class MlpNet : public Net {
 
   float *partials(StepCtx &c) const { return reinterpret_cast<float *>(c.ks + 256); }
 
-  // one launch: dW = x^T dr ([D_in, D_out] = [D, B] x [B, D]), dx = g + dr W^T
-  // and db, with dr = g [z > 0] formed as it is read
+  // dW = x^T dr ([D_in, D_out] = [D, B] x [B, D]), dx = g + dr W^T and db, with
+  // dr = g [z > 0]: one launch that forms dr as it is read, or dr into the
+  // scratch (with db) and the products one by one
   void bwd(int32_t i, const void *g, void *dx, const void *x, const void *, const void *saved,
-           void *, StepCtx &c) override {
+           void *q, StepCtx &c) override {
+    const float *gp = static_cast<const float *>(g), *zp = static_cast<const float *>(saved),
+                *xp = static_cast<const float *>(x);
+    float *dxp = static_cast<float *>(dx);
+    if (mlp_bwd_wins(B, D)) {
+      timer.begin(c.s);
+      c.launches += mlp_bwd(c.s, B, D, gp, zp, xp, P(c, wi[i]), dxp, G(c, wi[i]), G(c, bi[i]), partials(c));
+      const double two = dx ? 2 : 1;
+      timer.end(c.s, two * gf(B, D, D), two * gb(B, D, D, 4.0 * B * D));
+      return;
+    }
+    float *dr = static_cast<float *>(q);
+    mlp_colsum_long(c.s, B, D, gp, zp, G(c, bi[i]), partials(c), dr);
+    c.launches += 2;
+    products(c, i, dr, xp, dxp, dxp ? gp : nullptr);
+  }
+
+  // dW = x^T dr and, when dx is given, dx = dr W^T (+ add)
+  void products(StepCtx &c, int32_t i, const float *dr, const float *x, float *dx, const float *add) {
     timer.begin(c.s);
-    c.launches += mlp_bwd(c.s, B, D, static_cast<const float *>(g), static_cast<const float *>(saved),
-                          static_cast<const float *>(x), P(c, wi[i]), static_cast<float *>(dx), G(c, wi[i]),
-                          G(c, bi[i]), partials(c));
-    const double two = dx ? 2 : 1;
-    timer.end(c.s, two * gf(B, D, D), two * gb(B, D, D, 4.0 * B * D));
+    gemm_f32(c.s, D, D, B, x, D, true, dr, D, false, G(c, wi[i]), D, GEMM_EPI_STORE);
+    timer.end(c.s, gf(D, D, B), gb(D, D, B, 0));
+    c.launches += 1;
+    if (!dx) return;
+    timer.begin(c.s);
+    gemm_f32(c.s, B, D, D, dr, D, false, P(c, wi[i]), D, true, dx, D, add ? GEMM_EPI_ADD : GEMM_EPI_STORE, add, D);
+    timer.end(c.s, gf(B, D, D), gb(B, D, D, add ? 4.0 * B * D : 0));
+    c.launches += 1;
   }
 
   void head(const void *xn, void *g, StepCtx &c) override {
@@ -139,10 +160,16 @@ class MlpNet : public Net {
     }
     const int i = (v - 1) / 3, k = (v - 1) % 3;
     if (k == 0) {  // fully connected: dx = dy W^T, dW = x^T dy, db = column sums of dy
-      timer.begin(c.s);
-      c.launches += mlp_bwd(c.s, B, D, dy, nullptr, static_cast<const float *>(ins[0]), P(c, wi[i]), o, G(c, wi[i]),
-                            G(c, bi[i]), partials(c));
-      timer.end(c.s, 2 * gf(B, D, D), gb(B, D, D, 0) + gb(D, D, B, 0));
+      const float *x = static_cast<const float *>(ins[0]);
+      if (mlp_bwd_wins(B, D)) {
+        timer.begin(c.s);
+        c.launches += mlp_bwd(c.s, B, D, dy, nullptr, x, P(c, wi[i]), o, G(c, wi[i]), G(c, bi[i]), partials(c));
+        timer.end(c.s, 2 * gf(B, D, D), gb(B, D, D, 0) + gb(D, D, B, 0));
+        return;
+      }
+      products(c, i, dy, x, o, nullptr);
+      mlp_colsum_long(c.s, B, D, dy, nullptr, G(c, bi[i]), partials(c));
+      c.launches += 2;
     } else if (k == 1) {  // ReLU: the mask from its output
       ew_relu_bwd(c.s, t, dy, static_cast<const float *>(yv), o);
       c.launches += 1;

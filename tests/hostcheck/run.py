@@ -372,6 +372,7 @@ def dry_runs(quick):
     small = [dict(kind="mlp", depth=9, width=72, batch=37, name="mlp small"),
              dict(kind="mlp", depth=3, width=40, batch=9, name="mlp one-workgroup head"),
              dict(kind="mlp", depth=3, width=8, batch=1025, name="mlp many rows"),
+             dict(kind="mlp", depth=2, width=1028, batch=1017, name="mlp products"),
              dict(kind="resnet_basic", blocks_per_stage=2, base=8, batch=3, image=16, classes=7,
                   name="cifar small"),
              dict(kind="resnet_basic", blocks_per_stage=2, base=8, batch=3, image=16, classes=7,
