@@ -1,5 +1,5 @@
-// Fixed-order sums of weight-gradient partials as parts of a workgroup's work,
-// for kernels that run them beside something else.
+// Fixed-order sums of weight-gradient partials as a workgroup's work, for kernels
+// that run them alone or beside something else.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -17,7 +17,6 @@ __device__ __forceinline__ int xcd_grouped(int id, int G) {
   const int q = G / 8, r = G % 8, x = id % 8, k = id / 8;
   return x * q + (x < r ? x : r) + k;
 }
-
 
 __device__ __forceinline__ void add4(float4 &s, const float4 &v) {
   s.x += v.x;
