@@ -196,29 +196,32 @@ __global__ __launch_bounds__(256) void k_bn_finalize_sum(const double *__restric
 }
 
 // Block-major partials: a workgroup takes 8 consecutive channels (8 lanes read
-// 64 contiguous bytes of a partial's row) and splits the nb rows into 128
-// slices, slice s adding rows s, s + 128, ... in order, all its loads of up to
+// 64 contiguous bytes of a partial's row) and splits the nb rows into 8 NW
+// slices, slice s adding rows s, s + 8 NW, ... in order, all its loads of up to
 // four rounds in flight; the slices combine by a butterfly over the 8 of a
 // wavefront, then in wavefront order.  Its time is a launch and one or two load
 // latencies: with a workgroup per channel (8-byte loads from rows 2 J apart)
 // 784 rows of 256 channels took 7.0 us, with 16 slices per 16 channels 516 rows
-// of 512 channels 6.6; 5.7 and 4.3 so.
-template <bool FWD>
-__global__ __launch_bounds__(1024) void k_bn_finalize_rows(const double *__restrict__ part, int nb, int J,
-                                                           double m, float *__restrict__ out,
-                                                           float *__restrict__ dgamma,
-                                                           float *__restrict__ dbeta) {
-  __shared__ double r0[16][8], r1[16][8];
+// of 512 channels 6.6; 5.7 and 4.3 so.  Sixteen wavefronts, or four where the
+// rows do not fill more (the same sums: 7 rows of 1024 channels 3.1 and 2.8 us, 20
+// of 256 3.7 and 3.5).
+template <bool FWD, int NW>
+__global__ __launch_bounds__(64 * NW) void k_bn_finalize_rows(const double *__restrict__ part, int nb, int J,
+                                                              double m, float *__restrict__ out,
+                                                              float *__restrict__ dgamma,
+                                                              float *__restrict__ dbeta) {
+  constexpr int SL = 8 * NW;
+  __shared__ double r0[NW][8], r1[NW][8];
   const int cl = threadIdx.x % 8, sl = threadIdx.x / 8;
   const int j = blockIdx.x * 8 + cl;
   double a = 0, b = 0;
   if (j < J)
-    for (int k0 = sl; k0 < nb; k0 += 4 * 128) {
+    for (int k0 = sl; k0 < nb; k0 += 4 * SL) {
       double ta[4], tb[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const bool in = k0 + 128 * u < nb;
-        const double *row = part + size_t(in ? k0 + 128 * u : k0) * 2 * J + j;
+        const bool in = k0 + SL * u < nb;
+        const double *row = part + size_t(in ? k0 + SL * u : k0) * 2 * J + j;
         ta[u] = in ? row[0] : 0.0;
         tb[u] = in ? row[J] : 0.0;
       }
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(1024) void k_bn_finalize_rows(const double *__restr
   if (threadIdx.x < 8 && j < J) {
     double sa = 0, sb = 0;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < NW; ++t) {
       sa += r0[t][cl];
       sb += r1[t][cl];
     }
@@ -692,9 +695,12 @@ static void bn_finalize(hipStream_t s, const double *part, int nb, int J, int64_
     hipLaunchKernelGGL((k_bn_finalize<FWD, true>), dim3(J), dim3(256), 0, s, part, nb, J, double(m), out, dgamma, dbeta);
   else if (bn_per_channel(nb, J))
     hipLaunchKernelGGL((k_bn_finalize<FWD, false>), dim3(J), dim3(256), 0, s, part, nb, J, double(m), out, dgamma, dbeta);
+  else if (nb <= 32)
+    hipLaunchKernelGGL((k_bn_finalize_rows<FWD, 4>), dim3((J + 7) / 8), dim3(256), 0, s, part, nb, J, double(m), out,
+                       dgamma, dbeta);
   else
-    hipLaunchKernelGGL(k_bn_finalize_rows<FWD>, dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), out, dgamma,
-                       dbeta);
+    hipLaunchKernelGGL((k_bn_finalize_rows<FWD, 16>), dim3((J + 7) / 8), dim3(1024), 0, s, part, nb, J, double(m), out,
+                       dgamma, dbeta);
 }
 
 void bn_finalize_fwd(hipStream_t s, const double *part, int nb, int J, int64_t m, float *st,

@@ -60,7 +60,7 @@ def test_sum_partials(nb, count):
     assert np.array_equal(base.host(out), ref)
 
 
-@pytest.mark.parametrize("nb", [1, 127, 129, 784, 1024, 1025, 1568])
+@pytest.mark.parametrize("nb", [1, 32, 33, 127, 129, 784, 1024, 1025, 1568])
 @pytest.mark.parametrize("j", [8, 13, 64, 66, 512])
 def test_bn_finalize_rows(nb, j):
     K = base._K()
